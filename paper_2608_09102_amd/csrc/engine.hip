@@ -1566,7 +1566,7 @@ void iter_arnoldi(llg_ctx& c, int j) {
     // delayed reorthogonalization: one sweep for the dots, one for v_j and w'
     double* u = c.V + (int64_t)j * c.ld;
     launch_dcgs_dots(st, m, j, c.V, c.ld, u, c.w, c.part);
-    launch_dcgs_finish1(st, c.part, c.npart_vec, j, R, c.ks, c.host);
+    launch_dcgs_finish1(st, c.part, dots_blocks(m, j), j, R, c.ks);
     launch_dcgs_update(st, m, j, c.V, c.ld, c.ks.coef, u, c.w, c.V + (int64_t)(j + 1) * c.ld, c.part);
     launch_dcgs_finish2(st, c.part, c.npart_vec, j, R, c.ks, c.host);
     LCHK();
@@ -1634,7 +1634,7 @@ SolveOut fgmres(llg_ctx& c) {
     return so;
   }
   while (!so.converged && so.iters < c.opts.max_iters) {
-    launch_cycle_start(st, R, c.ks);
+    launch_cycle_start(st, R, c.ks, so.iters == 0);
     launch_scale_vec(st, m, c.r, c.ks.sc + 1, c.V);
     LCHK();
     // Pipelined iterations: after enqueuing the orthogonalization of column
@@ -1674,7 +1674,7 @@ SolveOut fgmres(llg_ctx& c) {
       // the last column is final once slot j is orthogonalized against v_0..v_{j-1}
       double* u = c.V + (int64_t)j * c.ld;
       launch_dcgs_dots(st, m, j, c.V, c.ld, u, u, c.part);
-      launch_dcgs_last(st, c.part, c.npart_vec, j, R, c.ks, H);
+      launch_dcgs_last(st, c.part, dots_blocks(m, j), j, R, c.ks, H);
       LCHK();
     }
     launch_solve_y(st, j, R, c.ks);

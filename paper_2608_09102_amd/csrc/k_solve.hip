@@ -840,6 +840,44 @@ __global__ void __launch_bounds__(TPB) k_mupdate_dot(int64_t m, const double* __
     part[(int64_t)threadIdx.x * G + blockIdx.x] = res[threadIdx.x];
 }
 
+// Sums of N values per lane over the wavefront, scattered: at each of the six
+// halving steps a lane keeps one half of the entries it still holds and sends
+// the other half across, so N values take about N shuffles instead of the 6 N
+// of N separate trees.  On return lane l holds `cnt` (0 or more) finished sums
+// in a[0..cnt), those of entries first..first+cnt.  A fixed tree.
+template <int N, int OFF>
+__device__ inline void wave_scatter_sums(double* a, int& first, int& cnt) {
+  constexpr int H = (N + 1) / 2;
+  const bool up = (threadIdx.x & OFF) != 0;
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const double lo = a[i], hi = i + H < N ? a[i + H < N ? i + H : 0] : 0.0;
+    a[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, OFF, 64);
+  }
+  first += up ? H : 0;
+  cnt = up ? max(0, cnt - H) : min(cnt, H);
+  if constexpr (OFF > 1) wave_scatter_sums<H, OFF / 2>(a, first, cnt);
+}
+
+// part[q][blk] of NS per-thread values, one column per workgroup of W waves.
+template <int NS, int W>
+__device__ inline void block_columns(double* acc, double* sh, double* __restrict__ part) {
+  int first = 0, cnt = NS;
+  wave_scatter_sums<NS, 32>(acc, first, cnt);
+  const int wv = threadIdx.x >> 6;
+  constexpr int LEFT = (NS + 63) / 64;
+#pragma unroll
+  for (int i = 0; i < LEFT; ++i)
+    if (i < cnt) sh[wv * NS + first + i] = acc[i];
+  __syncthreads();
+  if (threadIdx.x < NS) {
+    double r = 0;
+#pragma unroll
+    for (int k = 0; k < W; ++k) r += sh[k * NS + threadIdx.x];
+    part[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = r;
+  }
+}
+
 // Delayed reorthogonalization (classical Gram-Schmidt with the second pass of
 // v_j lagged into the next iteration, after Swirydowicz, Langou, Ananthan,
 // Yang and Thomas 2021).  Slot j of V holds u = h_j v~_j: the once
@@ -847,31 +885,57 @@ __global__ void __launch_bounds__(TPB) k_mupdate_dot(int64_t m, const double* __
 // the iteration, a second sweep finishes v_j and forms the next w'.
 // part[q] = V_q . u and part[NV + q] = V_q . w (q < NV), part[2NV] = u.u,
 // part[2NV + 1] = u.w, part[2NV + 2] = w.w, one column per workgroup.
+// Bound by HBM (8 (NV + 2) bytes per entry) on large vectors, by the reduction
+// of the 2 NV + 3 sums on small ones: two entries a lane as one 16-byte load,
+// the sums scattered over the lanes while they are added.  Measured against
+// one entry a lane and a shuffle tree per sum (mean over the iterations of a
+// solve): 13.2 -> 5.5 us at 64^2, 84 -> 68 us at 1024^2, 142 -> 120 us at
+// 128^3, 265 -> 272 us at 256^3 (four iterations, where neither counts).
+constexpr int DOTS_T = 512;
 template <int NV>
-__global__ void __launch_bounds__(TPB) k_dcgs_dots(int64_t m, const double* __restrict__ V, int64_t ldv,
-                                                   const double* __restrict__ u, const double* __restrict__ w,
-                                                   double* __restrict__ part) {
+__global__ void __launch_bounds__(DOTS_T) k_dcgs_dots(int64_t m, const double* __restrict__ V, int64_t ldv,
+                                                      const double* __restrict__ u, const double* __restrict__ w,
+                                                      double* __restrict__ part) {
   constexpr int NS = 2 * NV + 3;
-  __shared__ double sh[(TPB / 64) * NS];
-  __shared__ double res[NS];
-  const int G = gridDim.x;
+  __shared__ double sh[(DOTS_T / 64) * NS];
   double acc[NS];
 #pragma unroll
   for (int q = 0; q < NS; ++q) acc[q] = 0.0;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (int64_t)G * blockDim.x) {
-    const double uk = u[k], wk = w[k];
+  // pairs of entries: slots start at multiples of 256 B
+  const int64_t stride = (int64_t)gridDim.x * DOTS_T;
+  const int64_t k0 = (int64_t)blockIdx.x * DOTS_T + threadIdx.x;
+  const int64_t np = m >> 1;
+  int64_t k = k0;
+  for (; k < np; k += stride) {
+    const double2 uk = reinterpret_cast<const double2*>(u)[k], wk = reinterpret_cast<const double2*>(w)[k];
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
-      const double v = V[q * ldv + k];
-      acc[q] += v * uk;
-      acc[NV + q] += v * wk;
+      const double2 v = reinterpret_cast<const double2*>(V + q * ldv)[k];
+      acc[q] += v.x * uk.x;
+      acc[q] += v.y * uk.y;
+      acc[NV + q] += v.x * wk.x;
+      acc[NV + q] += v.y * wk.y;
     }
-    acc[2 * NV] += uk * uk;
-    acc[2 * NV + 1] += uk * wk;
-    acc[2 * NV + 2] += wk * wk;
+    acc[2 * NV] += uk.x * uk.x;
+    acc[2 * NV] += uk.y * uk.y;
+    acc[2 * NV + 1] += uk.x * wk.x;
+    acc[2 * NV + 1] += uk.y * wk.y;
+    acc[2 * NV + 2] += wk.x * wk.x;
+    acc[2 * NV + 2] += wk.y * wk.y;
   }
-  block_sums<NS>(acc, sh, res);
-  if (threadIdx.x < NS) part[(int64_t)threadIdx.x * G + blockIdx.x] = res[threadIdx.x];
+  if (k == np && (m & 1)) {  // the last entry of an odd length
+    const double ul = u[m - 1], wl = w[m - 1];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const double v = V[q * ldv + m - 1];
+      acc[q] += v * ul;
+      acc[NV + q] += v * wl;
+    }
+    acc[2 * NV] += ul * ul;
+    acc[2 * NV + 1] += ul * wl;
+    acc[2 * NV + 2] += wl * wl;
+  }
+  block_columns<NS, DOTS_T / 64>(acc, sh, part);
 }
 
 // v_j = du u - sum_q d_q V_q (over u, in place) and w' = w - sum_q c_q V_q - cu u
@@ -935,7 +999,15 @@ __global__ void k_zy(int64_t m, int kk, const TZ* __restrict__ Z, int64_t ldz, c
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= m) return;
   double a = u[k];
-  for (int q = 0; q < kk; ++q) a += y[q] * (double)Z[q * ldz + k];
+  int q = 0;
+  for (; q + 8 <= kk; q += 8) {  // eight loads in flight
+    double z[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) z[t] = (double)Z[(q + t) * ldz + k];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) a += y[q + t] * z[t];
+  }
+  for (; q < kk; ++q) a += y[q] * (double)Z[q * ldz + k];
   u[k] = a;
 }
 
@@ -1412,102 +1484,129 @@ __global__ void k_arnoldi_finish(const double* part, int64_t nparts, int j, int 
   for (int i = threadIdx.x; i <= j + 1; i += blockDim.x) ks.H[i * R + j] = col[i];
 }
 
-// Final column `col` (unrotated, rows 0..jj+1) of the Hessenberg matrix:
-// the previous rotations, a new one, the rotated column into H and the
-// right-hand side g updated.  Returns the residual estimate |g_{jj+1}|.
-// One thread.
-__device__ inline double givens_column(double* col, int jj, int R, KrylovScalars ks) {
+// Value x of lane i (uniform i), without a trip through LDS.
+__device__ inline double lane_value(double x, int i) {
+  const long long v = __double_as_longlong(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)v, i);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), i);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Sum of x over lanes 0..n-1 (n <= 64), all lanes, a fixed tree.
+__device__ inline double lanes_sum(double x, int n) {
+  double r = (int)(threadIdx.x & 63) < n ? x : 0.0;
+  for (int off = 32; off > 0; off >>= 1) r += __shfl_xor(r, off, 64);
+  return r;
+}
+
+// Final column jj (unrotated, rows 0..jj+1; row i in lane i) of the Hessenberg
+// matrix: the previous rotations, a new one, the rotated column into H and the
+// right-hand side g updated.  Returns the residual estimate |g_{jj+1}|.  One
+// wavefront: lane i brings its entry and rotation i (c, s), the chain of
+// rotations runs on values read across lanes; gj = g_jj.
+__device__ inline double givens_column(double col, double c, double s, double gj, int jj, int R, KrylovScalars ks) {
+  const int lane = threadIdx.x & 63;
+  double run = lane_value(col, 0);  // the entry the next rotation changes first
   for (int i = 0; i < jj; ++i) {
-    const double a = col[i], c = col[i + 1];
-    col[i] = ks.cs[i] * a + ks.sn[i] * c;
-    col[i + 1] = -ks.sn[i] * a + ks.cs[i] * c;
+    const double ci = lane_value(c, i), si = lane_value(s, i), nx = lane_value(col, i + 1);
+    const double top = ci * run + si * nx;
+    run = -si * run + ci * nx;
+    if (lane == i) col = top;
   }
-  const double a = col[jj], c = col[jj + 1];
-  const double rho = hypot(a, c);
-  const double cj = a / rho, sj = c / rho;
-  ks.cs[jj] = cj;
-  ks.sn[jj] = sj;
-  col[jj] = rho;
-  col[jj + 1] = 0.0;
-  const double gj = ks.g[jj];
-  ks.g[jj + 1] = -sj * gj;
-  ks.g[jj] = cj * gj;
-  for (int i = 0; i <= jj + 1; ++i) ks.H[i * R + jj] = col[i];
+  const double last = lane_value(col, jj + 1);
+  const double rho = hypot(run, last);
+  const double cj = run / rho, sj = last / rho;
+  if (lane == jj) col = rho;
+  if (lane == jj + 1) col = 0.0;
+  if (lane <= jj + 1) ks.H[lane * R + jj] = col;
+  if (lane == 0) {
+    ks.cs[jj] = cj;
+    ks.sn[jj] = sj;
+    ks.g[jj + 1] = -sj * gj;
+    ks.g[jj] = cj * gj;
+  }
   return fabs(sj * gj);
 }
 
 // After the dots sweep of iteration j: s = V^T v~_j, nu = |v~_j - V s| (by
 // Pythagoras), the coefficients of w against the final v_0..v_j, the final
 // column j-1 (its last entries change with v~_j = V s + nu v_j), and the
-// coefficients of the update sweep.
-__global__ void k_dcgs_finish1(const double* part, int64_t nparts, int j, int R, KrylovScalars ks, double* host) {
-  __shared__ double a[MAXV_S + 1], b[MAXV_S + 1], e3[3], col[MAXV_S + 2];
-  const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+// coefficients of the update sweep.  The sums are taken a column per wave;
+// one wave, an entry per lane, does the rest: with the operands in flight
+// beside the sums and the rotations run across lanes 6.4 us against 9.4 us on
+// one thread (64^2), 7.6 against 12.6 at 1024^2.
+__global__ void k_dcgs_finish1(const double* part, int64_t nparts, int j, int R, KrylovScalars ks) {
+  __shared__ double tot[2 * MAXV_S + 3];
+  const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6, lane = threadIdx.x & 63;
   const int ns = 2 * j + 3;
   for (int q = wv; q < ns; q += nw) {
     const double v = wave_sum(part + (int64_t)q * nparts, nparts);
-    if ((threadIdx.x & 63) == 0) {
-      if (q < j)
-        a[q] = v;
-      else if (q < 2 * j)
-        b[q - j] = v;
-      else
-        e3[q - 2 * j] = v;
-    }
+    if (lane == 0) tot[q] = v;
   }
+  // the wave's own operands, in flight with the partial sums
+  const double h = ks.hs[j], hc = lane < j ? ks.hcol[lane] : 0.0;
+  const double c = lane < j - 1 ? ks.cs[lane] : 0.0, s = lane < j - 1 ? ks.sn[lane] : 0.0;
+  const double gj = j > 0 ? ks.g[j - 1] : 0.0, passes = ks.sc[10];
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  const double h = ks.hs[j];
-  double nu = 1.0, ss = 0.0;
+  if (wv != 0) return;
+  const double a = lane < j ? tot[lane] / h : 0.0;  // s_q
+  const double b = lane < j ? tot[j + lane] : 0.0;
+  const double e0 = tot[2 * j], e1 = tot[2 * j + 1], e2 = tot[2 * j + 2];
+  double nu = 1.0;
   if (j > 0) {
-    for (int q = 0; q < j; ++q) {
-      a[q] /= h;  // s_q
-      ss += a[q] * a[q];
-    }
-    const double nu2 = e3[0] / (h * h) - ss;
+    const double nu2 = e0 / (h * h) - lanes_sum(a * a, j);
     nu = nu2 > 0.0 ? sqrt(nu2) : 0.0;
   }
-  double st = 0.0;
-  for (int q = 0; q < j; ++q) st += a[q] * b[q];
-  const double hjj = nu > 0.0 ? (e3[1] / h - st) / nu : 0.0;
-  if (j > 0) {  // column j-1 is final now
-    for (int q = 0; q < j; ++q) col[q] = ks.hcol[q] + h * a[q];
-    col[j] = h * nu;
-    ks.sc[3] = givens_column(col, j - 1, R, ks);
-    host[7] += 1.0;  // delayed second passes in this solve
-  }
-  for (int q = 0; q < j; ++q) ks.hcol[q] = b[q];
-  ks.hcol[j] = hjj;
+  const double st = lanes_sum(a * b, j);
+  const double hjj = nu > 0.0 ? (e1 / h - st) / nu : 0.0;
   // update sweep: v_j = u / (h nu) - V s / nu, w' = w - V (t - s hjj / nu) - u hjj / (h nu)
   const double inv = nu > 0.0 ? 1.0 / nu : 0.0;
-  for (int q = 0; q < j; ++q) {
-    ks.coef[q] = a[q] * inv;
-    ks.coef[j + q] = b[q] - a[q] * hjj * inv;
+  if (lane < j) {
+    ks.hcol[lane] = b;
+    ks.coef[lane] = a * inv;
+    ks.coef[j + lane] = b - a * hjj * inv;
   }
-  ks.coef[2 * j] = inv / h;
-  ks.coef[2 * j + 1] = hjj * inv / h;
-  ks.sc[5] = e3[2];  // ||w||^2
-  ks.sc[8] = nu > 0.0 ? 0.0 : 1.0;
+  if (lane == 0) {
+    ks.hcol[j] = hjj;
+    ks.coef[2 * j] = inv / h;
+    ks.coef[2 * j + 1] = hjj * inv / h;
+    ks.sc[5] = e2;  // ||w||^2
+    ks.sc[8] = nu > 0.0 ? 0.0 : 1.0;
+  }
+  if (j > 0) {  // column j-1 is final now
+    const double est = givens_column(lane < j ? hc + h * a : h * nu, c, s, gj, j - 1, R, ks);
+    if (lane == 0) {
+      ks.sc[3] = est;
+      ks.sc[10] = passes + 1.0;  // delayed second passes in this solve
+    }
+  }
 }
 
 // After the update sweep: h_{j+1} = |w'|, the provisional column j (its
 // first-pass entries) rotated by the final rotations for the residual
 // estimate, and the breakdown test.
 __global__ void k_dcgs_finish2(const double* part, int64_t nparts, int j, int R, KrylovScalars ks, double* host) {
-  const double s = wave_sum(part, nparts);
-  if (threadIdx.x != 0) return;
-  const double hn = sqrt(s);
-  ks.hs[j + 1] = hn;
-  ks.hinv[j + 1] = 1.0 / hn;  // slot j+1 times this is the next preconditioner input
-  ks.sc[4] = hn;
+  const int lane = threadIdx.x & 63;
+  const double hc = lane <= j ? ks.hcol[lane] : 0.0;
+  double c = 0.0, s = 0.0;
+  if (lane < j) {
+    c = ks.cs[lane];
+    s = ks.sn[lane];
+  }
+  const double gj = ks.g[j], w2 = ks.sc[5], lost = ks.sc[8];
+  const double hn = sqrt(lane_value(wave_sum(part, nparts), 0));
   // rotation i changes entries i and i+1 of the column; only the running
   // entry (i+1, the next rotation's input) is needed, and entry j+1 = hn is
   // untouched by rotations 0..j-1
-  double t = ks.hcol[0];
-  for (int i = 0; i < j; ++i) t = -ks.sn[i] * t + ks.cs[i] * ks.hcol[i + 1];
+  double t = lane_value(hc, 0);
+  for (int i = 0; i < j; ++i) t = -lane_value(s, i) * t + lane_value(c, i) * lane_value(hc, i + 1);
   const double rho = hypot(t, hn);
-  const double est = fabs(hn / rho * ks.g[j]);
-  const int breakdown = (hn <= 1e-14 * sqrt(ks.sc[5]) || ks.sc[8] != 0.0) ? 1 : 0;
+  const double est = fabs(hn / rho * gj);
+  const int breakdown = (hn <= 1e-14 * sqrt(w2) || lost != 0.0) ? 1 : 0;
+  if (lane != 0) return;
+  ks.hs[j + 1] = hn;
+  ks.hinv[j + 1] = 1.0 / hn;  // slot j+1 times this is the next preconditioner input
+  ks.sc[4] = hn;
   ks.sc[9] = (double)breakdown;
   host[3] = est;
   host[6] = (double)breakdown;
@@ -1517,41 +1616,37 @@ __global__ void k_dcgs_finish2(const double* part, int64_t nparts, int j, int R,
 // the dots of slot k against v_0..v_{k-1} (part from k_dcgs_dots<k> with
 // u = w = slot k); without correction after a breakdown.
 __global__ void k_dcgs_last(const double* part, int64_t nparts, int k, int R, KrylovScalars ks, double* host) {
-  __shared__ double a[MAXV_S + 1], uu[1], col[MAXV_S + 2];
-  const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  __shared__ double tot[MAXV_S + 1];
+  const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6, lane = threadIdx.x & 63;
   for (int q = wv; q <= k; q += nw) {
-    const int idx = q < k ? q : 2 * k;
-    const double v = wave_sum(part + (int64_t)idx * nparts, nparts);
-    if ((threadIdx.x & 63) == 0) {
-      if (q < k)
-        a[q] = v;
-      else
-        uu[0] = v;
-    }
+    const double v = wave_sum(part + (int64_t)(q < k ? q : 2 * k) * nparts, nparts);
+    if (lane == 0) tot[q] = v;
   }
+  const double h = ks.hs[k], hc = lane < k ? ks.hcol[lane] : 0.0;
+  const double c = lane < k - 1 ? ks.cs[lane] : 0.0, s = lane < k - 1 ? ks.sn[lane] : 0.0;
+  const double gj = ks.g[k - 1], lost = ks.sc[9];
+  double passes = ks.sc[10];
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  const double h = ks.hs[k];
-  const int j = k - 1;
-  if (ks.sc[9] != 0.0 || !(h > 0.0)) {
-    for (int q = 0; q <= j; ++q) col[q] = ks.hcol[q];
-    col[j + 1] = h;
+  if (wv != 0) return;
+  double col;
+  if (lost != 0.0 || !(h > 0.0)) {
+    col = lane < k ? hc : h;
   } else {
-    double ss = 0.0;
-    for (int q = 0; q < k; ++q) {
-      a[q] /= h;
-      ss += a[q] * a[q];
-    }
-    const double nu2 = uu[0] / (h * h) - ss;
-    for (int q = 0; q <= j; ++q) col[q] = ks.hcol[q] + h * a[q];
-    col[j + 1] = h * (nu2 > 0.0 ? sqrt(nu2) : 0.0);
-    host[7] += 1.0;
+    const double a = lane < k ? tot[lane] / h : 0.0;
+    const double nu2 = tot[k] / (h * h) - lanes_sum(a * a, k);
+    col = lane < k ? hc + h * a : h * (nu2 > 0.0 ? sqrt(nu2) : 0.0);
+    passes += 1.0;
   }
-  ks.sc[3] = givens_column(col, j, R, ks);
-  host[3] = ks.sc[3];
+  const double est = givens_column(col, c, s, gj, k - 1, R, ks);
+  if (lane == 0) {
+    ks.sc[3] = est;
+    ks.sc[10] = passes;
+    host[3] = est;
+    host[7] = passes;
+  }
 }
 
-__global__ void k_cycle_start(int R, KrylovScalars ks) {
+__global__ void k_cycle_start(int R, KrylovScalars ks, int first) {
   for (int i = threadIdx.x; i <= R; i += blockDim.x) ks.g[i] = 0.0;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -1560,17 +1655,27 @@ __global__ void k_cycle_start(int R, KrylovScalars ks) {
     ks.hs[0] = 1.0;  // v_0 = r / beta is final
     ks.hinv[0] = 1.0;
     ks.sc[9] = 0.0;
+    if (first) ks.sc[10] = 0.0;
   }
 }
 
-// y = H(0:k, 0:k)^{-1} g(0:k), upper triangular back substitution
+// y = H(0:k, 0:k)^{-1} g(0:k), upper triangular back substitution by one
+// wavefront: lane i keeps row i's running right-hand side and, once y_q is
+// known, takes H_iq y_q from it; the column of the next step is loaded ahead.
 __global__ void k_solve_y(int k, int R, KrylovScalars ks) {
-  if (threadIdx.x != 0) return;
-  for (int i = k - 1; i >= 0; --i) {
-    double s = ks.g[i];
-    for (int q = i + 1; q < k; ++q) s -= ks.H[i * R + q] * ks.y[q];
-    ks.y[i] = s / ks.H[i * R + i];
+  const int lane = threadIdx.x & 63;
+  double s = lane < k ? ks.g[lane] : 0.0;
+  const double d = lane < k ? ks.H[lane * R + lane] : 1.0;
+  double y = 0.0;
+  double h = lane < k - 1 ? ks.H[lane * R + k - 1] : 0.0;
+  for (int q = k - 1; q >= 0; --q) {
+    const double hn = q > 0 && lane < q - 1 ? ks.H[lane * R + q - 1] : 0.0;
+    const double yq = lane_value(s, q) / lane_value(d, q);
+    if (lane == q) y = yq;
+    s -= h * yq;
+    h = hn;
   }
+  if (lane < k) ks.y[lane] = y;
 }
 
 // ------------------------------------------------------ fused coarse cycle
@@ -2089,9 +2194,19 @@ void launch_mupdate_dot(hipStream_t st, int64_t m, int nv, const double* V, int6
 
 #define LLG_NV0_CASES(X) X(0) LLG_NV_CASES(X)
 
+// Workgroups of the dots sweep against nv vectors: about as many as are
+// resident at once (4 nv + 6 registers a thread hold the sums: two workgroups
+// of 8 waves a CU up to 25 vectors, one beyond), so that every workgroup
+// reduces its sums once and the scalar step reads few columns; fewer on short
+// vectors.  At most red_blocks(m), the room in part.
+int64_t dots_blocks(int64_t m, int nv) {
+  const int64_t cap = nv <= 25 ? 512 : 256;
+  return std::max<int64_t>(1, std::min<int64_t>({cap, red_blocks(m), ceil_div(m, 2 * DOTS_T)}));
+}
+
 void launch_dcgs_dots(hipStream_t st, int64_t m, int nv, const double* V, int64_t ldv, const double* u,
                       const double* w, double* part) {
-  const dim3 g((unsigned)red_blocks(m)), t(TPB);
+  const dim3 g((unsigned)dots_blocks(m, nv)), t(DOTS_T);
   switch (nv) {
 #define X(K) \
   case K: hipLaunchKernelGGL((k_dcgs_dots<K>), g, t, 0, st, m, V, ldv, u, w, part); break;
@@ -2113,9 +2228,8 @@ void launch_dcgs_update(hipStream_t st, int64_t m, int nv, const double* V, int6
   }
 }
 
-void launch_dcgs_finish1(hipStream_t st, const double* part, int64_t nparts, int j, int R, KrylovScalars ks,
-                         double* host) {
-  hipLaunchKernelGGL(k_dcgs_finish1, dim3(1), dim3(1024), 0, st, part, nparts, j, R, ks, host);
+void launch_dcgs_finish1(hipStream_t st, const double* part, int64_t nparts, int j, int R, KrylovScalars ks) {
+  hipLaunchKernelGGL(k_dcgs_finish1, dim3(1), dim3(1024), 0, st, part, nparts, j, R, ks);
 }
 void launch_dcgs_finish2(hipStream_t st, const double* part, int64_t nparts, int j, int R, KrylovScalars ks,
                          double* host) {
@@ -2162,8 +2276,8 @@ void launch_arnoldi_finish_n(hipStream_t st, const double* part, int64_t nparts,
                              KrylovScalars ks, double* host) {
   hipLaunchKernelGGL(k_arnoldi_finish, dim3(1), dim3(64), 0, st, part, nparts, j, R, ks, host);
 }
-void launch_cycle_start(hipStream_t st, int R, KrylovScalars ks) {
-  hipLaunchKernelGGL(k_cycle_start, dim3(1), dim3(64), 0, st, R, ks);
+void launch_cycle_start(hipStream_t st, int R, KrylovScalars ks, bool first) {
+  hipLaunchKernelGGL(k_cycle_start, dim3(1), dim3(64), 0, st, R, ks, first ? 1 : 0);
 }
 void launch_solve_y(hipStream_t st, int k, int R, KrylovScalars ks) {
   hipLaunchKernelGGL(k_solve_y, dim3(1), dim3(64), 0, st, k, R, ks);

@@ -527,11 +527,13 @@ struct KrylovScalars {
   double* hcol;   // R+1 (dots of the current pass)
   double* y;      // R
   double* sc;     // scalars: [0] beta, [1] 1/beta or 1/h, [2] bnorm, [3] est, [4] hn, [5] wnorm0,
-                  // [7] second pass asked (two-pass form), [8] [9] breakdown flags (delayed form)
+                  // [7] second pass asked (two-pass form), [8] [9] breakdown flags and [10] second
+                  // passes of the solve (delayed form)
   double* hs;     // R+2: delayed form, slot j of V holds hs[j] times the once-orthogonalized v~_j
   double* hinv;   // R+2: the scale of slot j for the preconditioner input
   double* coef;   // 2R+4: coefficients of the update sweep
 };
+int64_t dots_blocks(int64_t m, int nv);  // partial-sum count of the delayed form's dots sweep against nv vectors
 int64_t red_blocks(int64_t m);  // partial-sum count of the grid reductions over m doubles
 void launch_norm_finish_n(hipStream_t st, const double* part, int64_t nparts, int slot, double* sc,
                           double* host);
@@ -542,15 +544,14 @@ void launch_reorth_finish_n(hipStream_t st, const double* part, int64_t nparts, 
                             double* delta, double* sc);
 void launch_arnoldi_finish_n(hipStream_t st, const double* part, int64_t nparts, int j, int R,
                              KrylovScalars ks, double* host);
-void launch_cycle_start(hipStream_t st, int R, KrylovScalars ks);
+void launch_cycle_start(hipStream_t st, int R, KrylovScalars ks, bool first);  // first: of a solve
 // Delayed reorthogonalization: the dots sweep (u = slot j, w = A z_j, nv = j),
 // its scalar step, the update sweep (v_j over u, w' into wo = slot j+1), its
 // scalar step; and at the end of a cycle of k iterations the dots of slot k
 // (u = w = slot k, nv = k) and the final last column.
 void launch_dcgs_dots(hipStream_t st, int64_t m, int nv, const double* V, int64_t ldv, const double* u,
                       const double* w, double* part);
-void launch_dcgs_finish1(hipStream_t st, const double* part, int64_t nparts, int j, int R, KrylovScalars ks,
-                         double* host);
+void launch_dcgs_finish1(hipStream_t st, const double* part, int64_t nparts, int j, int R, KrylovScalars ks);
 void launch_dcgs_update(hipStream_t st, int64_t m, int nv, const double* V, int64_t ldv, const double* coef,
                         double* u, const double* w, double* wo, double* part);
 void launch_dcgs_finish2(hipStream_t st, const double* part, int64_t nparts, int j, int R, KrylovScalars ks,
