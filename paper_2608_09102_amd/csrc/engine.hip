@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -28,6 +29,7 @@
 
 #include "../../include/llg.h"
 #include "llg_internal.h"
+#include "team.h"
 
 namespace llg {
 
@@ -216,6 +218,7 @@ struct StructSet {
   LevelStruct lv[LLG_MAX_LEVELS];
   int L = 0;
   int32_t *flags = nullptr, *count = nullptr, *scan_tmp = nullptr;
+  void* ops = nullptr;  // the team's steps on this set's structure
 };
 
 struct PlanKey {
@@ -270,6 +273,13 @@ struct llg_ctx {
   bool tail_ok = false;
   llg::TailArgs<double> ta64{};
   llg::TailArgs<float> ta32{};
+  // levels team.. run their cycle as one launch of a team (0: none): its steps
+  // (two lists when there are two structure sets), state and XCD
+  int team = 0;
+  int nops = 0, ntouch = 0, tlines = 0;
+  void *ops = nullptr, *ops2 = nullptr;
+  llg::TeamState* team_st = nullptr;
+  int team_xcd = 0;
   double* Mh = nullptr;
   double* mt = nullptr;  // factored grid level: the frozen field, from which the solve kernels recompute blocks
   // coarsest
@@ -752,6 +762,7 @@ void save_struct(const llg_ctx& c, StructSet& S) {
   S.flags = c.flags;
   S.count = c.count;
   S.scan_tmp = c.scan_tmp;
+  S.ops = c.ops;
   for (int l = 0; l < LLG_MAX_LEVELS; ++l) {
     const Level& L = c.lv[l];
     LevelStruct& T = S.lv[l];
@@ -780,6 +791,7 @@ void load_struct(llg_ctx& c, const StructSet& S) {
   c.flags = S.flags;
   c.count = S.count;
   c.scan_tmp = S.scan_tmp;
+  c.ops = S.ops;
   for (int l = 0; l < LLG_MAX_LEVELS; ++l) {
     Level& L = c.lv[l];
     const LevelStruct& T = S.lv[l];
@@ -912,6 +924,11 @@ void allocate_numeric(llg_ctx& c, Arena& ar) {
     plan_tail<float>(c, c.ta32);
   else
     plan_tail<double>(c, c.ta64);
+  c.team_st = (TeamState*)ar.get(sizeof(TeamState), true);
+  const size_t op = f32 ? sizeof(TeamOp<float>) : sizeof(TeamOp<double>);
+  const size_t list = TEAM_OPS * op + TEAM_TOUCH * sizeof(TeamTouch);
+  c.ops = ar.get(list, true);
+  if (overlapped_rebuild(c.opts)) c.ops2 = ar.get(list, true);
   if (c.opts.stray_field) {
     c.fd = field_dims(c.grid.n[0], c.grid.n[1], c.grid.n[2]);
     const int64_t P = c.fd.px * c.fd.py * c.fd.pz;
@@ -997,6 +1014,266 @@ std::shared_ptr<Plan> get_plan(const llg_grid& g, const llg_opts& o) {
   std::lock_guard<std::mutex> lk(g_plan_mu);
   g_plans[key] = plan;
   return plan;
+}
+
+// ------------------------------------------------------- the team's steps
+// The cycle of levels c.team..L-1 as the list of steps a team runs: the same
+// recursion as vcycle, vcycle_gs and kcorrection, one entry for each launch
+// those make (the K-cycle's coefficients are part of the steps that use them).
+template <typename T>
+struct TeamList {
+  llg_ctx& c;
+  std::vector<TeamOp<T>> ops;
+
+  TeamOp<T>& add(TeamKind kind, int64_t n) {
+    ops.push_back(TeamOp<T>{});
+    ops.back().kind = kind;
+    ops.back().n = (int32_t)n;
+    return ops.back();
+  }
+  void matrix(TeamOp<T>& o, const Level& L) {
+    o.G = L.G;
+    o.i0 = L.brp;
+    o.i1 = L.bci;
+    o.val = (const T*)L.vt;
+    o.dinv = (const T*)L.dinv;
+  }
+  // P^T r onto level l (r null: the launch's argument), with the first
+  // pre-smoothing sweep from x = 0 when the level starts with one
+  void restrict_to(int l, const T* r, bool sweep) {
+    const Level &F = c.lv[l - 1], &L = c.lv[l];
+    TeamOp<T>& o = add(TK_RESTRICT, F.nc);
+    o.i0 = F.mptr;
+    o.i1 = F.mem;
+    o.b = r;
+    o.out = (T*)L.b;
+    if (sweep) {
+      o.dinv = (const T*)L.dinv;
+      o.out2 = (T*)L.x;
+    }
+  }
+  void dense(const int32_t* mptr, const int32_t* mem, const T* r, T* out) {
+    TeamOp<T>& o = add(TK_DENSE, c.nd / 3);
+    o.i0 = mptr;
+    o.i1 = mem;
+    o.b = r;
+    o.out = out;
+    o.inv = c.dense;
+  }
+  void sweep(int l, const T* b, const T* x, T* out) {
+    const Level& L = c.lv[l];
+    TeamOp<T>& o = add(TK_SWEEP, L.A.n);
+    matrix(o, L);
+    o.b = b;
+    o.x = x;
+    o.out = out;
+  }
+  // x' = x (0 when null) + P e_{l+1} on level l into xp (x itself or a free
+  // vector): by the step that finishes e_{l+1} when it is a sweep or the
+  // coarsest solve
+  void prolong_into(int l, const T* x, T* xp) {
+    const Level &L = c.lv[l], &Nx = c.lv[l + 1];
+    TeamOp<T>& o = ops.back();
+    if ((o.kind == TK_SWEEP || o.kind == TK_DENSE) && o.out == (const T*)Nx.e && (!x || x == xp)) {
+      o.px = xp;
+      o.p0 = L.mptr;
+      o.p1 = L.mem;
+      o.pz = x ? 0 : 1;
+    } else {
+      prolong(l, x, (const T*)Nx.e, xp);
+    }
+  }
+  void residual(int l, const T* b, const T* x) {
+    const Level& L = c.lv[l];
+    TeamOp<T>& o = add(TK_RESIDUAL, L.A.n);
+    matrix(o, L);
+    o.b = b;
+    o.x = x;
+    o.out = (T*)L.r;
+  }
+  void prolong(int l, const T* x, const T* ec, T* out) {
+    const Level& L = c.lv[l];
+    TeamOp<T>& o = add(TK_PROLONG, L.A.n);
+    o.x = x;
+    o.ec = ec;
+    o.agg = L.agg;
+    o.out = out;
+  }
+  bool first_sweep() const { return c.opts.nu_pre >= 1 && c.opts.smoother == LLG_SMOOTHER_JACOBI; }
+  void correction(int l) {
+    if (c.lv[l].kc)
+      kcycle(l);
+    else
+      cycle(l, (const T*)c.lv[l].b, (T*)c.lv[l].e);
+  }
+  void cycle(int l, const T* b, T* out) {
+    if (l == c.L - 1) {
+      dense(nullptr, nullptr, b, out);
+      return;
+    }
+    if (c.opts.smoother == LLG_SMOOTHER_MCGS) {
+      cycle_gs(l, b, out);
+      return;
+    }
+    const Level &L = c.lv[l], &Nx = c.lv[l + 1];
+    const llg_opts& o = c.opts;
+    T *X = (T*)L.x, *XO = (T*)L.xo;
+    const T* xcur = o.nu_pre >= 1 ? X : nullptr;  // null: x = 0
+    for (int q = 1; q < o.nu_pre; ++q) {
+      T* dst = xcur == X ? XO : X;
+      sweep(l, b, xcur, dst);
+      xcur = dst;
+    }
+    const T* r = b;
+    if (xcur) {
+      residual(l, b, xcur);
+      r = (const T*)L.r;
+    }
+    if (l + 2 == c.L) {
+      dense(L.mptr, L.mem, r, (T*)Nx.e);
+    } else {
+      restrict_to(l + 1, r, first_sweep());
+      correction(l + 1);
+    }
+    if (o.nu_post == 0) {
+      prolong(l, xcur, (const T*)Nx.e, out);
+      return;
+    }
+    T* xp = xcur == XO ? XO : X;
+    prolong_into(l, xcur, xp);
+    xcur = xp;
+    for (int q = 0; q < o.nu_post; ++q) {
+      T* dst = q == o.nu_post - 1 ? out : (xcur == XO ? X : XO);
+      sweep(l, b, xcur, dst);
+      xcur = dst;
+    }
+  }
+  void gs_sweeps(const Level& L, const T* b, T* x, bool forward, bool first) {
+    for (int q = 0; q < L.ncol; ++q) {
+      const int k = forward ? q : L.ncol - 1 - q;
+      if (L.cls[k].n <= 0) continue;
+      TeamOp<T>& o = add(first && q == 0 ? TK_GS_FIRST : TK_GS, L.cls[k].n);
+      o.G = L.G;
+      o.i0 = L.cls[k].sl_ptr;
+      o.i1 = L.cls[k].col;
+      o.rows = L.perm + L.coff[k];
+      o.val = (const T*)L.cval[k];
+      o.dinv = (const T*)L.cdinv[k];
+      o.b = b;
+      o.out = x;
+    }
+  }
+  void cycle_gs(int l, const T* b, T* out) {
+    const Level &L = c.lv[l], &Nx = c.lv[l + 1];
+    T* X = (T*)L.x;
+    add(TK_ZERO, L.A.n).out = X;
+    for (int q = 0; q < c.opts.nu_pre; ++q) gs_sweeps(L, b, X, true, q == 0);
+    const T* r = b;
+    if (c.opts.nu_pre >= 1) {
+      residual(l, b, X);
+      r = (const T*)L.r;
+    }
+    restrict_to(l + 1, r, false);
+    correction(l + 1);
+    prolong(l, X, (const T*)Nx.e, out);
+    for (int q = 0; q < c.opts.nu_post; ++q) gs_sweeps(L, b, out, false, false);
+  }
+  void spmv_dots(const Level& C, const T* v, T* w, const T* d1, const T* d2) {
+    TeamOp<T>& o = add(TK_SPMV_DOTS, C.A.n);
+    matrix(o, C);
+    o.np = (int32_t)rows_blocks(C.A.n, C.G);
+    o.x = v;
+    o.out = w;
+    o.b = d1;
+    o.ec = d2;
+    o.part = c.part;
+  }
+  void kcycle(int l) {
+    const Level& C = c.lv[l];
+    const int32_t G = (int32_t)rows_blocks(C.A.n, C.G);
+    cycle(l, (const T*)C.b, (T*)C.v1);
+    spmv_dots(C, (const T*)C.v1, (T*)C.w1, (const T*)C.b, nullptr);
+    {
+      TeamOp<T>& o = add(TK_KC_UPDATE, C.A.n);
+      o.np = G;
+      o.part = c.part;
+      o.part2 = C.prho;
+      o.kc = C.kc;
+      o.b = (const T*)C.b;
+      o.x = (const T*)C.w1;
+      o.dinv = (const T*)C.dinv;
+      o.out = (T*)C.rho;
+      o.out2 = first_sweep() ? (T*)C.x : nullptr;
+    }
+    cycle(l, (const T*)C.rho, (T*)C.v2);
+    spmv_dots(C, (const T*)C.v2, (T*)C.w2, (const T*)C.w1, (const T*)C.rho);
+    TeamOp<T>& o = add(TK_KC_COMBINE, C.A.n);
+    o.np = G;
+    o.part = c.part;
+    o.part2 = C.prho;
+    o.kc = C.kc;
+    o.b = (const T*)C.v1;
+    o.x = (const T*)C.v2;
+    o.out = (T*)C.e;
+  }
+};
+
+// The levels a team runs: from the first coarse level whose matrix takes at
+// most TEAM_BYTES (and from level 2 when level 1 goes through the grid level)
+// to the coarsest.  A smaller level is bound by the latency of its steps, 2 us
+// each in the team against 4.5-6 us as a kernel; a larger one by the one L2 it
+// would have instead of eight.  Both sides measured (preconditioner, us): with
+// a level of 0.7 MB (1258 nodes, 3D FP32) 358 in the team and 360 outside,
+// 1.0 MB (2019 nodes, 2D FP64) 162 and 168, 2.2 MB (1881 nodes, 3D FP64) 738
+// and 730, 2.3 MB (8441 nodes, 2D FP32) 350 and 343, 3.4 MB (2D FP64) 177 and
+// 165, 9.1 MB (3D FP32) 384 and 361.  Off with tail_nodes = 0, which asks for
+// the levels one by one.  Called once the structure in c is the set the list
+// is for.
+template <typename T>
+void plan_team(llg_ctx& c, void* dev) {
+  c.team = 0;
+  int s = c.f1 ? 2 : 1;
+  while (s < c.L && (c.lv[s].A.n >= 32768 || c.lv[s].nnzb * (int64_t)(9 * sizeof(T) + 4) > TEAM_BYTES)) ++s;
+  if (c.opts.tail_nodes <= 0 || s > c.L - 2) return;
+  TeamList<T> t{c, {}};
+  t.restrict_to(s, nullptr, t.first_sweep());
+  t.correction(s);
+  if ((int)t.ops.size() > TEAM_OPS) return;  // deep K-cycles: level by level
+  c.team = s;
+  c.nops = (int)t.ops.size();
+  c.ops = dev;
+  // what the first use would wait for, smallest level first
+  std::vector<TeamTouch> touch;
+  int64_t lines = 0;
+  auto add = [&](const void* p, int64_t bytes) {
+    if ((int)touch.size() == TEAM_TOUCH) return;
+    touch.push_back(TeamTouch{(const int32_t*)p, lines});
+    lines += ceil_div(bytes, 128);
+  };
+  add(dev, (int64_t)(t.ops.size() * sizeof(TeamOp<T>)));
+  add(c.dense, c.nd * c.nd * (int64_t)sizeof(double));
+  for (int l = c.L - 2; l >= s; --l) {
+    const Level& L = c.lv[l];
+    add(L.mptr, (L.nc + 1) * 4);
+    add(L.mem, L.A.n * 4);
+    add(L.brp, (L.A.n + 1) * 4);
+    add(L.bci, L.nnzb * 4);
+    add(L.vt, L.nnzb * 9 * (int64_t)sizeof(T));
+    add(L.dinv, L.A.nslices * SL * 9 * (int64_t)sizeof(T));
+  }
+  c.ntouch = (int)touch.size();
+  c.tlines = (int)std::min<int64_t>(lines, TEAM_WARM * TEAM_T * TEAM_W);
+  TeamTouch* td = (TeamTouch*)((char*)dev + TEAM_OPS * sizeof(TeamOp<T>));
+  HIPX(hipMemcpyAsync(td, touch.data(), touch.size() * sizeof(TeamTouch), hipMemcpyHostToDevice, c.st));
+  HIPX(hipMemcpyAsync(dev, t.ops.data(), t.ops.size() * sizeof(TeamOp<T>), hipMemcpyHostToDevice, c.st));
+  HIPX(hipStreamSynchronize(c.st));
+}
+
+void plan_team(llg_ctx& c, void* dev) {
+  if (c.opts.precision == LLG_PREC_FP32_AMG)
+    plan_team<float>(c, dev);
+  else
+    plan_team<double>(c, dev);
 }
 
 // ------------------------------------------------------------------ setup
@@ -1334,6 +1611,17 @@ void kcorrection(llg_ctx& c, int lc);
 template <typename T>
 void vcycle_gs(llg_ctx& c, int l, const T* b, T* out);
 
+// The correction of level c.team (into its e) from the residual r of the
+// level above, by the team.
+template <typename T>
+void team_correction(llg_ctx& c, const T* r) {
+  KTimer kt(c, LLG_KT_SMOOTH);
+  const TeamOp<T>* ops = (const TeamOp<T>*)c.ops;
+  launch_team<T>(c.st, c.team_st, c.team_xcd, ops, c.nops, c.omega, (int)c.nd, (const TeamTouch*)(ops + TEAM_OPS),
+                 c.ntouch, c.tlines, r);
+  LCHK();
+}
+
 template <typename T>
 void vcycle(llg_ctx& c, int l, const T* b, T* out) {
   hipStream_t st = c.st;
@@ -1378,7 +1666,8 @@ void vcycle(llg_ctx& c, int l, const T* b, T* out) {
     LCHK();
   }
   const bool coarsest_next = l + 1 == c.L - 1;
-  const bool tail_next = c.tail > 0 && l + 1 == c.tail;  // the rest of the cycle in one workgroup
+  const bool team_next = c.team > 0 && l + 1 == c.team;  // the rest of the cycle by a team
+  const bool tail_next = !team_next && c.tail > 0 && l + 1 == c.tail;  // or in one workgroup
   const T* rsrc = b;
   {
     KTimer kt(c, LLG_KT_RESIDUAL);
@@ -1387,7 +1676,7 @@ void vcycle(llg_ctx& c, int l, const T* b, T* out) {
       lvl_residual<T>(c, l, xmode, b, xcur, (T*)L.r);
       rsrc = (const T*)L.r;
     }
-    if (tail_next) {
+    if (team_next || tail_next) {
       // the fused cycle restricts rsrc itself
     } else if (coarsest_next) {  // restriction and the exact coarsest solve in one launch
       launch_restrict_dense<T>(st, L.nc, L.mptr, L.mem, rsrc, c.dense, (T*)Nx.e);
@@ -1397,7 +1686,9 @@ void vcycle(llg_ctx& c, int l, const T* b, T* out) {
     }
     LCHK();
   }
-  if (tail_next) {
+  if (team_next) {
+    team_correction<T>(c, rsrc);
+  } else if (tail_next) {
     KTimer kt(c, LLG_KT_SMOOTH);
     launch_tail<T>(st, tail_args<T>(c), rsrc, L.mptr, L.mem, (T*)Nx.e);
     LCHK();
@@ -1450,6 +1741,7 @@ void vcycle_gs(llg_ctx& c, int l, const T* b, T* out) {
   Level& L = c.lv[l];
   Level& Nx = c.lv[l + 1];
   const llg_opts& o = c.opts;
+  const bool team_next = c.team > 0 && l + 1 == c.team;
   T* X = (T*)L.x;
   {
     KTimer kt(c, LLG_KT_SMOOTH);
@@ -1464,13 +1756,19 @@ void vcycle_gs(llg_ctx& c, int l, const T* b, T* out) {
       lvl_residual<T>(c, l, 0, b, X, (T*)L.r);
       rsrc = (const T*)L.r;
     }
-    launch_restrict<T>(st, L.nc, L.mptr, L.mem, rsrc, (T*)Nx.b, nullptr, c.omega, nullptr);
+    if (team_next)
+      team_correction<T>(c, rsrc);
+    else
+      launch_restrict<T>(st, L.nc, L.mptr, L.mem, rsrc, (T*)Nx.b, nullptr, c.omega, nullptr);
     LCHK();
   }
-  if (Nx.kc)
+  if (team_next) {
+    // Nx.e holds the coarse correction
+  } else if (Nx.kc) {
     kcorrection<T>(c, l + 1);
-  else
+  } else {
     vcycle<T>(c, l + 1, (const T*)Nx.b, (T*)Nx.e);
+  }
   KTimer kt(c, LLG_KT_SMOOTH);
   launch_prolong<T>(st, L.A.n, 0, c.omega, b, X, L.agg, (const T*)Nx.e, out);
   for (int s = 0; s < o.nu_post; ++s) gs_sweeps<T>(c, L, b, out, false, false);
@@ -2016,6 +2314,12 @@ llg_status llg_create(const llg_grid* grid, const llg_opts* opts, void* d_worksp
     c->L = build_structure(*c, ar);
     allocate_numeric(*c, ar);
     c->used = ar.off;
+    launch_fill_i32(c->st, (int32_t*)c->team_st, sizeof(TeamState) / sizeof(int32_t), 0);
+    LCHK();
+    static std::atomic<unsigned> contexts{0};  // contexts take the XCDs in turn
+    c->team_xcd = (int)(contexts.fetch_add(1, std::memory_order_relaxed) % 8);
+    void* ops1 = c->ops;
+    plan_team(*c, ops1);
     int32_t fl1 = 0;
     if (plan->dbl) {  // the second structure set, built here as well
       c->dbl = true;
@@ -2030,6 +2334,7 @@ llg_status llg_create(const llg_grid* grid, const llg_opts* opts, void* d_worksp
       a2.st = c->st;
       (void)build_structure(*c, a2);
       c->used += a2.off;
+      plan_team(*c, c->ops2);
       save_struct(*c, c->sets[1]);
       HIPX(hipMemcpyAsync(c->hflags, c->flags, sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
       HIPX(hipStreamSynchronize(c->st));

@@ -10,6 +10,7 @@
 #include <algorithm>
 
 #include "llg_internal.h"
+#include "team.h"
 
 namespace llg {
 
@@ -52,13 +53,18 @@ __device__ inline V3<T> xval(const T* x, const T* b, T omega, int64_t j) {
   return V3<T>{T(0), T(0), T(0)};
 }
 
-// acc += blk * v for a 3x3 block stored slot-major
-template <typename T, typename TV, typename TA>
+// acc += blk * v for a 3x3 block whose entries are ST apart (slot-major: SL).
+// The products' order is written out, so that every kernel that takes a row
+// this way rounds it the same.
+template <int ST = SL, typename T, typename TV, typename TA>
 __device__ inline void blk_mv(const T* __restrict__ val, int64_t vb, V3<TV> v, TA& a0, TA& a1, TA& a2) {
   const TA x = (TA)v.x, y = (TA)v.y, z = (TA)v.z;
-  a0 += (TA)val[vb + 0 * SL] * x + (TA)val[vb + 1 * SL] * y + (TA)val[vb + 2 * SL] * z;
-  a1 += (TA)val[vb + 3 * SL] * x + (TA)val[vb + 4 * SL] * y + (TA)val[vb + 5 * SL] * z;
-  a2 += (TA)val[vb + 6 * SL] * x + (TA)val[vb + 7 * SL] * y + (TA)val[vb + 8 * SL] * z;
+  TA m[9];
+#pragma unroll
+  for (int e = 0; e < 9; ++e) m[e] = (TA)val[vb + e * ST];
+  a0 += __builtin_elementwise_fma(m[2], z, __builtin_elementwise_fma(m[1], y, m[0] * x));
+  a1 += __builtin_elementwise_fma(m[5], z, __builtin_elementwise_fma(m[4], y, m[3] * x));
+  a2 += __builtin_elementwise_fma(m[8], z, __builtin_elementwise_fma(m[7], y, m[6] * x));
 }
 
 // Nine zero entries per lane at the slot stride: the block that padding slots
@@ -1317,8 +1323,14 @@ __device__ inline double wave_sum(const double* __restrict__ part, int64_t npart
 // whole workgroup (TPB-multiple size): every thread loads its entries of all
 // columns before the first add; lanes, then waves, are added in a fixed
 // tree.  The totals land in tot[0..NQ) (shared), valid after the call.
-template <int NQ>
-__device__ inline void group_sums(const double* __restrict__ part, int64_t ld, int64_t n, double* tot) {
+struct PlainLoad {
+  __device__ double operator()(const double* p) const { return *p; }
+};
+struct TeamLoad {  // partial sums of other members of a team
+  __device__ double operator()(const double* p) const { return team_ld(p); }
+};
+template <int NQ, typename LD = PlainLoad>
+__device__ inline void group_sums(const double* part, int64_t ld, int64_t n, double* tot) {
   __shared__ double ws[32][NQ];
   const int nt = (int)blockDim.x, nw = nt >> 6, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   double a[NQ][4];
@@ -1333,7 +1345,7 @@ __device__ inline void group_sums(const double* __restrict__ part, int64_t ld, i
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int64_t k = k0 + (int64_t)u * nt + threadIdx.x;
-        v[q][u] = k < n ? part[q * ld + k] : 0.0;
+        v[q][u] = k < n ? LD()(part + q * ld + k) : 0.0;
       }
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
@@ -1847,6 +1859,338 @@ __global__ void __launch_bounds__(TAIL_T) k_tail(const TailArgs<T> a, const T* _
   }
 }
 
+// ------------------------------------------------- small levels by a team
+// Entry i of a vector that other members write, past the L1 as team_ld, in one
+// request (FP32) or two instead of one per component; p is the same for all
+// lanes.  The XCD's L2 takes one request a clock and channel, and the x
+// gathers of a step are most of them.
+typedef unsigned tu2 __attribute__((ext_vector_type(2)));
+typedef unsigned tu3 __attribute__((ext_vector_type(3)));
+typedef unsigned tu4 __attribute__((ext_vector_type(4)));
+constexpr int CPOL_SC1 = 16;  // cache policy of device scope
+__device__ inline __amdgpu_buffer_rsrc_t team_rsrc(const void* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00027000);
+}
+__device__ inline V3<float> tl3(const float* p, int64_t i) {
+  const tu3 v = __builtin_amdgcn_raw_buffer_load_b96(team_rsrc(p), (int)i * 12, 0, CPOL_SC1);
+  return V3<float>{__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z)};
+}
+__device__ inline V3<double> tl3(const double* p, int64_t i) {
+  const __amdgpu_buffer_rsrc_t r = team_rsrc(p);
+  const tu4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)i * 24, 0, CPOL_SC1);
+  const tu2 w = __builtin_amdgcn_raw_buffer_load_b64(r, (int)i * 24 + 16, 0, CPOL_SC1);
+  return V3<double>{__hiloint2double((int)v.y, (int)v.x), __hiloint2double((int)v.w, (int)v.z),
+                    __hiloint2double((int)w.y, (int)w.x)};
+}
+
+// f(i, sub) for the rows of a step, G lanes a row: wavefront w of member r
+// takes every (16 n)-th stretch of 64 / G rows, members first, so that few
+// rows are spread over many CUs.
+template <int G, typename F>
+__device__ inline void team_rows(const Team& t, int n, F f) {
+  const int lane = threadIdx.x & 63;
+  const int w = (int)(threadIdx.x >> 6) * (int)t.n + (int)t.rank, nw = (TEAM_T / 64) * (int)t.n;
+  for (int i0 = w * (64 / G); i0 < n; i0 += nw * (64 / G)) {
+    const int i = i0 + lane / G;
+    if (i < n) f(i, lane % G);
+  }
+}
+
+// The row product of step o (x through xf), G lanes a row: the level's blocks
+// in CSR order (a wavefront's rows are contiguous there; the slices would
+// have it touch a line per slot and entry, four to eight times as many), the
+// colour classes of Gauss-Seidel in slices.
+template <int G, typename T, typename XF>
+__device__ inline V3<T> team_row_mv(const TeamOp<T>& o, int i, int sub, XF xf) {
+  T a0 = 0, a1 = 0, a2 = 0;
+  if (o.kind == TK_GS) {
+    const int s = i / SL, l = i - s * SL;
+    const int64_t cb = o.i0[s];
+    const int w = (int)((o.i0[s + 1] - cb) / SL);
+    sell_row_mv_g<G>(o.i1, o.val, cb, w, l, sub, xf, a0, a1, a2);
+  } else {
+    // the same blocks a lane, in the same order, as in slices
+    const int32_t k1 = o.i0[i + 1];
+    for (int32_t k = o.i0[i] + sub; k < k1; k += 2 * G) {
+      const bool two = k + G < k1;
+      const int32_t c0 = o.i1[k], c1 = two ? o.i1[k + G] : 0;
+      blk_mv<1>(o.val, (int64_t)k * 9, xf(c0), a0, a1, a2);
+      if (two) blk_mv<1>(o.val, (int64_t)(k + G) * 9, xf(c1), a0, a1, a2);
+    }
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) {
+      a0 += __shfl_xor(a0, off, G);
+      a1 += __shfl_xor(a1, off, G);
+      a2 += __shfl_xor(a2, off, G);
+    }
+  }
+  return V3<T>{a0, a1, a2};
+}
+
+// The entries of a finished correction e_i go to the members of aggregate i
+// on the level above, x' = x + P e, by the row's own lanes (one or two members
+// each): the sweep there then gathers x' alone, instead of an aggregate and
+// its correction behind every neighbour.
+template <int G, typename T>
+__device__ inline void team_spread(const TeamOp<T>& o, int i, int sub, V3<T> e) {
+  const int32_t q1 = o.p0[i + 1];
+  for (int32_t q = o.p0[i] + sub; q < q1; q += G) {
+    const int64_t j = o.p1[q];
+    V3<T> xi = o.pz ? V3<T>{T(0), T(0), T(0)} : tl3((const T*)o.px, j);
+    xi.x += e.x;
+    xi.y += e.y;
+    xi.z += e.z;
+    st3(o.px, j, xi);
+  }
+}
+
+// D_i^{-1} of a step's rows
+template <typename T>
+__device__ inline B9<T> team_dinv(const TeamOp<T>& o, int i) {
+  const int s = i / SL;
+  return ld9(o.dinv, (int64_t)s * 9 * SL + (i - s * SL));
+}
+template <typename T>
+__device__ inline V3<T> dmv9(const B9<T>& d, V3<T> v) {
+  return V3<T>{d.e[0] * v.x + d.e[1] * v.y + d.e[2] * v.z, d.e[3] * v.x + d.e[4] * v.y + d.e[5] * v.z,
+               d.e[6] * v.x + d.e[7] * v.y + d.e[8] * v.z};
+}
+
+template <int G, typename T>
+__device__ inline void team_matrix_step(const Team& t, const TeamOp<T>& o, T om, double* sh) {
+  const V3<T> zero{T(0), T(0), T(0)};
+  if (o.kind == TK_RESIDUAL) {
+    team_rows<G>(t, o.n, [&](int i, int sub) {
+      const V3<T> b = tl3(o.b, (int64_t)i);
+      const V3<T> a = team_row_mv<G>(o, i, sub, [&](int32_t c) { return tl3(o.x, (int64_t)c); });
+      if (sub == 0) st3(o.out, (int64_t)i, V3<T>{b.x - a.x, b.y - a.y, b.z - a.z});
+    });
+  } else if (o.kind == TK_SWEEP) {
+    // the row's own operands are on their way with the row
+    team_rows<G>(t, o.n, [&](int i, int sub) {
+      const V3<T> b = tl3(o.b, (int64_t)i);
+      const V3<T> xi = o.x ? tl3(o.x, (int64_t)i) : zero;
+      const B9<T> d = team_dinv(o, i);
+      const V3<T> a = o.x ? team_row_mv<G>(o, i, sub, [&](int32_t c) { return tl3(o.x, (int64_t)c); }) : zero;
+      const V3<T> res = dmv9(d, V3<T>{b.x - a.x, b.y - a.y, b.z - a.z});
+      const V3<T> v{xi.x + om * res.x, xi.y + om * res.y, xi.z + om * res.z};
+      if (sub == 0) st3(o.out, (int64_t)i, v);
+      if (o.px) team_spread<G>(o, i, sub, v);
+    });
+  } else if (o.kind == TK_GS) {
+    team_rows<G>(t, o.n, [&](int k, int sub) {
+      const int64_t i = o.rows[k];
+      const V3<T> b = tl3(o.b, i), xi = tl3((const T*)o.out, i);
+      const B9<T> d = team_dinv(o, k);
+      const V3<T> a = team_row_mv<G>(o, k, sub, [&](int32_t c) { return tl3((const T*)o.out, (int64_t)c); });
+      const V3<T> res = dmv9(d, V3<T>{b.x - a.x, b.y - a.y, b.z - a.z});
+      if (sub == 0) st3(o.out, i, V3<T>{xi.x + res.x, xi.y + res.y, xi.z + res.z});
+    });
+  } else {  // TK_SPMV_DOTS: blocks of 256 threads, as the per-level launch has them
+    const int grp = (int)(threadIdx.x >> 8), gt = (int)(threadIdx.x & 255), lane = gt & 63, wv = gt >> 6;
+    const int nb = o.np, ND = o.ec ? 2 : 1;
+    for (int v0 = 0; v0 < nb; v0 += 4 * (int)t.n) {
+      const int vb = v0 + grp * (int)t.n + (int)t.rank;
+      const int i = (vb * 256 + gt) / G, sub = gt % G;
+      double acc[3] = {0.0, 0.0, 0.0};
+      if (vb < nb && i < o.n) {
+        const V3<T> d = tl3(o.b, (int64_t)i), e = o.ec ? tl3(o.ec, (int64_t)i) : zero;
+        const V3<T> a = team_row_mv<G>(o, i, sub, [&](int32_t c) { return tl3(o.x, (int64_t)c); });
+        if (sub == 0) {
+          st3(o.out, (int64_t)i, a);
+          const double x0 = a.x, x1 = a.y, x2 = a.z;
+          acc[0] = (x0 * x0 + x1 * x1) + x2 * x2;
+          acc[1] = (x0 * (double)d.x + x1 * (double)d.y) + x2 * (double)d.z;
+          acc[2] = (x0 * (double)e.x + x1 * (double)e.y) + x2 * (double)e.z;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        double a = acc[q];
+        for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
+        if (lane == 0) sh[(grp * 4 + wv) * 3 + q] = a;
+      }
+      __syncthreads();
+      if (gt <= ND && vb < nb) {
+        double r = 0;
+        for (int k = 0; k < 4; ++k) r += sh[(grp * 4 + k) * 3 + gt];
+        o.part[(int64_t)gt * nb + vb] = r;
+      }
+      __syncthreads();
+    }
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(TEAM_T) k_team(TeamState* ts, int pick, const TeamOp<T>* __restrict__ ops, int nops,
+                                                 T om, int nd, const TeamTouch* __restrict__ touch, int ntouch,
+                                                 int lines, const T* rarg) {
+  extern __shared__ double sb[];  // the coarsest right-hand side (nd)
+  __shared__ double sh[(TEAM_T / 64) * 3];
+  __shared__ double tot[4];
+  Team t;
+  if (!t.join(ts, (unsigned)pick)) return;
+  const int tid = (int)threadIdx.x;
+  // The levels' matrices to the XCD's L2, a word of every line, while the
+  // first steps (restrictions) run: what comes cold costs the small levels as
+  // much as their work.  The words are dropped after the first step.
+  int32_t warm[TEAM_WARM];
+#pragma unroll
+  for (int a = 0; a < TEAM_WARM; ++a) {
+    const int line = (a * TEAM_T + tid) * (int)t.n + (int)t.rank;
+    warm[a] = 0;
+    if (line < lines) {
+      const int32_t* p = touch[0].p + (int64_t)line * 32;
+      for (int e = 1; e < ntouch; ++e)
+        if (line >= touch[e].first) p = touch[e].p + (int64_t)(line - touch[e].first) * 32;
+      warm[a] = *p;
+    }
+  }
+  auto each = [&](int n, auto f) { team_rows<1>(t, n, [&](int i, int) { f(i); }); };
+  auto sum_members = [&](const int32_t* mptr, const int32_t* mem, const T* r, int I) {
+    T a0 = 0, a1 = 0, a2 = 0;
+    for (int32_t q = mptr[I]; q < mptr[I + 1]; ++q) {
+      const V3<T> v = tl3(r, (int64_t)mem[q]);
+      a0 += v.x;
+      a1 += v.y;
+      a2 += v.z;
+    }
+    return V3<T>{a0, a1, a2};
+  };
+  auto first_sweep = [&](const TeamOp<T>& o, int i, V3<T> v) {
+    const int s = i / SL;
+    const V3<T> d = dmv(o.dinv, (int64_t)s * 9 * SL + (i - s * SL), v);
+    st3(o.out2, (int64_t)i, V3<T>{om * d.x, om * d.y, om * d.z});
+  };
+  TeamOp<T> o = ops[0];
+  for (int k = 0; k < nops; ++k) {
+    const T* r = o.b ? o.b : rarg;
+    switch (o.kind) {
+      case TK_RESTRICT:
+        each(o.n, [&](int I) {
+          const V3<T> a = sum_members(o.i0, o.i1, r, I);
+          st3(o.out, (int64_t)I, a);
+          if (o.out2) first_sweep(o, I, a);
+        });
+        break;
+      case TK_PROLONG:
+        each(o.n, [&](int i) {
+          V3<T> xi = o.x ? tl3(o.x, (int64_t)i) : V3<T>{T(0), T(0), T(0)};
+          const V3<T> e = tl3(o.ec, (int64_t)o.agg[i]);
+          st3(o.out, (int64_t)i, V3<T>{xi.x + e.x, xi.y + e.y, xi.z + e.z});
+        });
+        break;
+      case TK_DENSE: {
+        // every member forms the whole right-hand side, then takes its rows
+        if (o.i0) {
+          for (int I = tid; I < o.n; I += TEAM_T) {
+            const V3<T> a = sum_members(o.i0, o.i1, r, I);
+            sb[3 * I] = (double)a.x;
+            sb[3 * I + 1] = (double)a.y;
+            sb[3 * I + 2] = (double)a.z;
+          }
+        } else {
+          for (int c = tid; c < nd; c += TEAM_T) sb[c] = (double)team_ld(r + c);
+        }
+        __syncthreads();
+        {
+#pragma clang fp contract(off)
+          const int lane = tid & 63;
+          for (int row = (tid >> 6) * (int)t.n + (int)t.rank; row < nd; row += (TEAM_T / 64) * (int)t.n) {
+            double s = 0.0;
+            for (int c = lane; c < nd; c += 64) s += o.inv[(int64_t)row * nd + c] * sb[c];
+            for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+            if (lane == 0) o.out[row] = (T)s;
+            if (o.px) {  // component row % 3 of the members' x' = x + P e
+              const T e = (T)__shfl(s, 0, 64);
+              const int I = row / 3, cmp = row - 3 * I;
+              const int32_t q = o.p0[I] + lane;
+              if (q < o.p0[I + 1]) {
+                T* xp = o.px + 3 * (int64_t)o.p1[q] + cmp;
+                *xp = o.pz ? T(0) + e : team_ld((const T*)xp) + e;
+              }
+            }
+          }
+        }
+        break;
+      }
+      case TK_KC_UPDATE: {
+        group_sums<2, TeamLoad>(o.part, o.np, o.np, tot);
+        const double w11 = tot[0], a1d = tot[1] / tot[0];
+        if (t.rank == 0 && tid == 0) {
+          o.kc[0] = a1d;
+          o.kc[1] = w11;
+        }
+        const T a1 = (T)a1d;
+        const int grp = tid >> 8, gt = tid & 255, lane = gt & 63, wv = gt >> 6;
+        const int nb = (o.n + 255) / 256;
+        for (int v0 = 0; v0 < nb; v0 += 4 * (int)t.n) {
+          const int vb = v0 + grp * (int)t.n + (int)t.rank;
+          const int i = vb * 256 + gt;
+          double acc = 0.0;
+          if (i < o.n) {  // vb >= nb: i >= n
+            const V3<T> ri = tl3(o.b, (int64_t)i), wi = tl3(o.x, (int64_t)i);
+            const V3<T> p{ri.x - a1 * wi.x, ri.y - a1 * wi.y, ri.z - a1 * wi.z};
+            st3(o.out, (int64_t)i, p);
+            acc = ((double)wi.x * p.x + (double)wi.y * p.y) + (double)wi.z * p.z;
+            if (o.out2) first_sweep(o, i, p);
+          }
+          for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+          if (lane == 0) sh[grp * 4 + wv] = acc;
+          __syncthreads();
+          if (gt == 0 && vb < nb) {
+            double r2 = 0;
+            for (int q = 0; q < 4; ++q) r2 += sh[grp * 4 + q];
+            o.part2[vb] = r2;
+          }
+          __syncthreads();
+        }
+        break;
+      }
+      case TK_KC_COMBINE: {
+        const double kc0 = team_ld(o.kc), w11 = team_ld(o.kc + 1);
+        group_sums<3, TeamLoad>(o.part, o.np, o.np, tot);
+        const int nb = (o.n + 255) / 256;
+        group_sums<1, TeamLoad>(o.part2, nb, nb, tot + 3);
+        const double w22 = tot[0], w12 = tot[1], w2r = tot[2], w1rho = tot[3];
+        const double gamma = w12 / w11;
+        const double num = w2r - gamma * w1rho;
+        const double den = (w22 - 2.0 * gamma * w12) + gamma * gamma * w11;
+        const double a2 = num / den;
+        const T c1 = (T)(kc0 - a2 * gamma), c2 = (T)a2;
+        each(3 * o.n, [&](int i) { o.out[i] = c1 * team_ld(o.b + i) + c2 * team_ld(o.x + i); });
+        break;
+      }
+      case TK_GS_FIRST:
+        each(o.n, [&](int q) {
+          const int64_t i = o.rows[q];
+          const int s = q / SL;
+          st3(o.out, i, dmv(o.dinv, (int64_t)s * 9 * SL + (q - s * SL), tl3(o.b, i)));
+        });
+        break;
+      case TK_ZERO:
+        each(3 * o.n, [&](int i) { o.out[i] = T(0); });
+        break;
+      default:
+        if (o.G == 16)
+          team_matrix_step<16>(t, o, om, sh);
+        else
+          team_matrix_step<8>(t, o, om, sh);
+    }
+    if (k == 0) {
+#pragma unroll
+      for (int a = 0; a < TEAM_WARM; ++a) asm volatile("" ::"v"(warm[a]));
+    }
+    if (k + 1 == nops) break;
+    // the next step's entry comes while the stores are acknowledged
+    const TeamOp<T> nx = ops[k + 1];
+    asm volatile("" ::"s"(nx.kind), "s"(nx.i0), "s"(nx.val), "s"(nx.x), "s"(nx.out), "s"(nx.p0));
+    t.barrier();
+    o = nx;
+  }
+  t.leave();
+}
+
 }  // namespace
 
 // ------------------------------------------------------------- launchers
@@ -1971,6 +2315,16 @@ void launch_tail(hipStream_t st, const TailArgs<T>& a, const T* rabove, const in
                  T* out) {
   hipLaunchKernelGGL((k_tail<T>), dim3(1), dim3(TAIL_T), (size_t)a.lds, st, a, rabove, mptr, mem, out);
 }
+template <typename T>
+void launch_team(hipStream_t st, TeamState* ts, int pick, const TeamOp<T>* ops, int nops, double omega, int nd,
+                 const TeamTouch* touch, int ntouch, int lines, const T* r) {
+  hipLaunchKernelGGL((k_team<T>), dim3(8 * TEAM_W), dim3(TEAM_T), nd * sizeof(double), st, ts, pick, ops, nops,
+                     (T)omega, nd, touch, ntouch, lines, r);
+}
+template void launch_team<double>(hipStream_t, TeamState*, int, const TeamOp<double>*, int, double, int,
+                                  const TeamTouch*, int, int, const double*);
+template void launch_team<float>(hipStream_t, TeamState*, int, const TeamOp<float>*, int, double, int,
+                                 const TeamTouch*, int, int, const float*);
 template void launch_tail<double>(hipStream_t, const TailArgs<double>&, const double*, const int32_t*,
                                   const int32_t*, double*);
 template void launch_tail<float>(hipStream_t, const TailArgs<float>&, const float*, const int32_t*, const int32_t*,

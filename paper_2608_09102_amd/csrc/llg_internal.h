@@ -395,6 +395,55 @@ void launch_tail(hipStream_t st, const TailArgs<T>& a, const T* rabove, const in
 // the tail kernel's LDS limit; false when the device refuses it
 bool tail_prepare();
 
+// The cycle of the small levels as one launch of a team (see team.h): a list
+// of steps, each what one per-level kernel does, with a team barrier after
+// each step.  Bound by the latency of a step's dependent loads and the
+// acknowledgement of its stores: about 2 us a step, 1024^2 (levels of 2658
+// nodes and fewer, 17 steps) 36 us against 66 us as kernels, the 64^2 K-cycle
+// (23 steps) 56 us against 105 us.  The rows of a step keep their lane groups and their order of
+// additions, and the partial sums of the K-cycle their 256-thread blocks, so
+// the result is that of the per-level kernels bit for bit.
+enum TeamKind : int32_t {
+  TK_RESTRICT,    // out = P^T r (mptr, mem); out2 = omega D^{-1} out when out2
+  TK_RESIDUAL,    // out = b - A x
+  TK_SWEEP,       // out = x + omega D^{-1} (b - A x), x = 0 when null
+  TK_PROLONG,     // out = x (0 when null) + ec[agg]
+  TK_DENSE,       // out = A_c^{-1} (P^T r) (mptr, mem), or A_c^{-1} r when mptr is null
+  TK_SPMV_DOTS,   // out = A x, part: out.out, out.b, out.ec (when ec)
+  TK_KC_UPDATE,   // a1 from part; out = b - a1 x, out2 = omega D^{-1} out when out2; part2: x.out
+  TK_KC_COMBINE,  // the weights from part and part2; out = c1 b + c2 x
+  TK_GS,          // one colour class: x_i += D_i^{-1} (b_i - sum_j A_ij x_j), in place in out
+  TK_GS_FIRST,    // the same from x = 0: x_i = D_i^{-1} b_i
+  TK_ZERO         // out = 0
+};
+template <typename T>
+struct TeamOp {
+  int32_t kind, n, G, np;             // rows; lanes per row; partial sums per column of part (K-cycle)
+  const int32_t *i0, *i1, *agg;       // row pointers and columns (TK_GS: of the slices), or mptr and mem
+  const int32_t* rows;                // TK_GS: rows of the class
+  const T *val, *dinv, *b, *x, *ec;   // r (TK_RESTRICT, TK_DENSE; null: the launch's argument) in b
+  T *out, *out2;
+  // TK_SWEEP, TK_DENSE: with px, px_j += out_i for the members j of aggregate
+  // i of the level above (p0, p1: its mptr and mem; pz: px counts as 0)
+  T* px;
+  const int32_t *p0, *p1;
+  int64_t pz;
+  double *part, *part2, *kc;
+  const double* inv;
+};
+constexpr int TEAM_OPS = 1024;         // longest list
+constexpr int64_t TEAM_BYTES = 2 << 20;  // largest level's matrix (see plan_team)
+struct TeamTouch {  // an array to bring to the XCD's L2 at the start: its first line of 128 bytes in the count of all
+  const int32_t* p;
+  int64_t first;
+};
+constexpr int TEAM_TOUCH = 128;        // most of them
+constexpr int TEAM_WARM = 2;           // lines a thread may take
+struct TeamState;
+template <typename T>
+void launch_team(hipStream_t st, TeamState* ts, int pick, const TeamOp<T>* ops, int nops, double omega, int nd,
+                 const TeamTouch* touch, int ntouch, int lines, const T* r);
+
 // b0 = D0^{-1} (v vs[0]) (or v vs[0]; vs NULL: 1), cast to T
 template <typename T>
 void launch_scale_in(hipStream_t st, int64_t n, const double* dinv0, int left_scale, const double* v,
