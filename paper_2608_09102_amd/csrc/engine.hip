@@ -87,6 +87,8 @@ struct Arena {
   hipStream_t st = nullptr;
   int32_t* flag = nullptr;        // REPLAY: mismatch flag
   int flag_word = 0;              // word of the flags the checks raise (1: a rebuild on the second stream)
+  std::vector<BuildLevel>* rec = nullptr;  // REPLAY at creation: the steps of the levels a team builds
+  int team_from = LLG_MAX_LEVELS;          // REPLAY of a step: the levels from here on are built by a team
   bool keep_grid = false;         // REPLAY of a step: the grid graph and the grid level's pattern (field and
                                   // aggregation independent) are already in place; skip their kernels
   int32_t* hcount = nullptr;      // PLAN: pinned read-back slot
@@ -218,7 +220,8 @@ struct StructSet {
   LevelStruct lv[LLG_MAX_LEVELS];
   int L = 0;
   int32_t *flags = nullptr, *count = nullptr, *scan_tmp = nullptr;
-  void* ops = nullptr;  // the team's steps on this set's structure
+  void* ops = nullptr;    // the team's steps on this set's structure
+  void* build = nullptr;  // and the lists of its build
 };
 
 struct PlanKey {
@@ -280,6 +283,11 @@ struct llg_ctx {
   void *ops = nullptr, *ops2 = nullptr;
   llg::TeamState* team_st = nullptr;
   int team_xcd = 0;
+  // the levels whose structure a team builds (from build_from on), a list per
+  // structure set, and the state of the stream that rebuilds
+  int build_from = LLG_MAX_LEVELS, nbuild = 0;
+  void *build = nullptr, *build2 = nullptr;
+  llg::TeamState* build_st = nullptr;
   double* Mh = nullptr;
   double* mt = nullptr;  // factored grid level: the frozen field, from which the solve kernels recompute blocks
   // coarsest
@@ -508,6 +516,11 @@ void build_colours(llg_ctx& c, Arena& ar, int l) {
 // Grid pattern, then per level: npass handshake-matching passes on the
 // integer graph, composite aggregates, member lists, next-level graph and
 // block pattern.  Returns the number of levels.
+//
+// Levels of at most BUILD_NODES nodes are built by a team in one launch
+// (launch_team_build), where a level takes 30 to 60 launches otherwise; a
+// context records their buffers when it is created (ar.rec) and its steps
+// launch the team at the first of them.  Larger levels fill the chip.
 int build_structure(llg_ctx& c, Arena& ar) {
   hipStream_t st = c.st;
   const llg_grid& g = c.grid;
@@ -550,6 +563,18 @@ int build_structure(llg_ctx& c, Arena& ar) {
     Level& L = c.lv[l];
     const int64_t n = L.A.n;
     if (n <= o.max_coarse || l + 1 >= o.max_levels) break;
+    const bool run = l < ar.team_from;
+    if (l == ar.team_from) {
+      launch_team_build(st, c.build_st, (c.team_xcd + 4) % 8, (const BuildLevel*)c.build, c.nbuild, o.npass, o.beta_num,
+                        o.beta_den, ar.flag, F_PLAN, c.dbl);
+      LCHK();
+    }
+    BuildLevel* rec = nullptr;
+    if (ar.rec && n <= BUILD_NODES) {
+      ar.rec->push_back(BuildLevel{});
+      rec = &ar.rec->back();
+      if (ar.rec->size() == 1) c.build_from = l;
+    }
     int32_t* acc = ar.alloc<int32_t>(n);
     const int32_t* leads[MAX_PASS] = {};
     const int32_t* mates[MAX_PASS] = {};
@@ -570,10 +595,13 @@ int build_structure(llg_ctx& c, Arena& ar) {
       int32_t* aggp = ar.alloc<int32_t>(cn);
       int32_t* lead = ar.alloc<int32_t>(cn);
       uint64_t* rank = on_grid ? ar.alloc<uint64_t>(cn) : nullptr;
-      if (on_grid)
+      if (!run) {
+        // by the team
+      } else if (on_grid) {
         launch_node_rank(st, cn, salt, rank);
-      else if (!preset)
+      } else if (!preset) {
         launch_match_init(st, cn, crp, cw, salt, ns, mate, prop);
+      }
       LCHK();
       // lanes per node in a proposal round: about two slots per lane on the
       // coarse levels (latency bound), one lane on the grid-sized levels.  A
@@ -591,7 +619,9 @@ int build_structure(llg_ctx& c, Arena& ar) {
       // handshake rounds: PLAN runs until a round has no proposal and logs
       // the number of rounds; REPLAY runs that many and checks the extra
       // round proposes nothing
-      if (cn <= MATCH_SMALL) {
+      if (!run) {
+        if (cn > MATCH_SMALL) ++ar.ci;
+      } else if (cn <= MATCH_SMALL) {
         // a small level: every round in one workgroup, in both modes
         launch_match_small(st, cn, crp, cci, cw, mate, ns, salt, o.beta_num, o.beta_den, prop, ar.flag, F_PLAN,
                            lanes);
@@ -623,15 +653,19 @@ int build_structure(llg_ctx& c, Arena& ar) {
         launch_check_eq(st, c.count, 0, ar.flag, F_PLAN);
         LCHK();
       }
-      launch_leader_flag(st, cn, mate, id);
-      launch_scan_excl(st, id, id, cn, id + cn, c.scan_tmp);
-      LCHK();
+      if (run) {
+        launch_leader_flag(st, cn, mate, id);
+        launch_scan_excl(st, id, id, cn, id + cn, c.scan_tmp);
+        LCHK();
+      }
       const int64_t nc = ar.count(id + cn);
-      launch_assign(st, cn, mate, id, aggp, lead);
       int32_t* cnt = ar.alloc<int32_t>(nc + 1);
-      launch_cg_count(st, nc, lead, mate, crp, cnt);
-      launch_scan_excl(st, cnt, cnt, nc, cnt + nc, c.scan_tmp);
-      LCHK();
+      if (run) {
+        launch_assign(st, cn, mate, id, aggp, lead);
+        launch_cg_count(st, nc, lead, mate, crp, cnt);
+        launch_scan_excl(st, cnt, cnt, nc, cnt + nc, c.scan_tmp);
+        LCHK();
+      }
       const int64_t ncand = ar.count(cnt + nc);
       int32_t* cj = ar.alloc<int32_t>(ncand);
       int32_t* cwt = ar.alloc<int32_t>(ncand);
@@ -649,15 +683,28 @@ int build_structure(llg_ctx& c, Arena& ar) {
       ns_next = ar.alloc<NodeSt>(nc);
       mate_next = ar.alloc<int32_t>(nc);
       prop_next = ar.alloc<int32_t>(nc);
-      launch_cg_fill(st, nc, lead, mate, crp, cci, cw, aggp, cnt, cj, cwt, nrp, ttot, wide,
-                     from_grid ? gdims : nullptr, ns_next, mate_next, prop_next);
-      launch_scan_excl(st, ttot, ttot, tiles, ttot + tiles, c.scan_tmp);
-      LCHK();
+      if (run) {
+        launch_cg_fill(st, nc, lead, mate, crp, cci, cw, aggp, cnt, cj, cwt, nrp, ttot, wide,
+                       from_grid ? gdims : nullptr, ns_next, mate_next, prop_next);
+        launch_scan_excl(st, ttot, ttot, tiles, ttot + tiles, c.scan_tmp);
+        LCHK();
+      }
       const int64_t ng = ar.count(ttot + tiles);
       int32_t* nci = ar.alloc<int32_t>(ng);
       int32_t* nw = ar.alloc<int32_t>(ng);
-      launch_cg_copy(st, nc, shape, cnt, cj, cwt, ttot, nrp, nci, nw);
-      LCHK();
+      if (run) {
+        launch_cg_copy(st, nc, shape, cnt, cj, cwt, ttot, nrp, nci, nw);
+        LCHK();
+      }
+      if (rec) {
+        // the grid level's first pass keeps its records where the per-pass
+        // kernels keep ranks (8 bytes a node both)
+        rec->pass[p] = BuildPass{(int32_t)cn, (int32_t)nc, (int32_t)ncand, (int32_t)ng, preset ? 0 : 1,
+                                 crp, cci, cw,
+                                 ns ? ns : (NodeSt*)rank,
+                                 mate, prop, id, aggp, lead, cnt, cj, cwt, nrp, nci, nw, ttot + tiles,
+                                 ns_next, mate_next, prop_next, salt};
+      }
       leads[p] = lead;
       mates[p] = mate;
       cn = nc;
@@ -670,10 +717,12 @@ int build_structure(llg_ctx& c, Arena& ar) {
     // members of the composite aggregates, ascending, and the composite map
     int32_t* mptr = ar.alloc<int32_t>(cn + 1);
     int32_t* mem = ar.alloc<int32_t>(n);
-    launch_member_count(st, cn, o.npass, leads, mates, mptr);
-    launch_scan_excl(st, mptr, mptr, cn, mptr + cn, c.scan_tmp);
-    launch_member_fill(st, cn, o.npass, leads, mates, mptr, mem, acc);
-    LCHK();
+    if (run) {
+      launch_member_count(st, cn, o.npass, leads, mates, mptr);
+      launch_scan_excl(st, mptr, mptr, cn, mptr + cn, c.scan_tmp);
+      launch_member_fill(st, cn, o.npass, leads, mates, mptr, mem, acc);
+      LCHK();
+    }
     L.agg = acc;
     L.mptr = mptr;
     L.mem = mem;
@@ -684,8 +733,23 @@ int build_structure(llg_ctx& c, Arena& ar) {
     Nx.gci = cci;
     Nx.gw = cw;
     Nx.gnnz = cg;
-    build_sell(ar, st, Nx, cn, cg);
-    finish_sell(ar, st, Nx, c.scan_tmp);
+    build_sell(ar, st, Nx, cn, cg, run);
+    finish_sell(ar, st, Nx, c.scan_tmp, run);
+    if (rec) {
+      rec->n = (int32_t)n;
+      rec->nc = (int32_t)cn;
+      rec->nslots = (int32_t)Nx.A.nslots;
+      rec->next = 1;
+      rec->mptr = mptr;
+      rec->mem = mem;
+      rec->acc = acc;
+      rec->grp = crp;
+      rec->gci = cci;
+      rec->brp = Nx.brp;
+      rec->bci = Nx.bci;
+      rec->sl = Nx.A.sl_ptr;
+      rec->col = Nx.A.col;
+    }
   }
   ar.flush_checks();
   return l + 1;
@@ -763,6 +827,7 @@ void save_struct(const llg_ctx& c, StructSet& S) {
   S.count = c.count;
   S.scan_tmp = c.scan_tmp;
   S.ops = c.ops;
+  S.build = c.build;
   for (int l = 0; l < LLG_MAX_LEVELS; ++l) {
     const Level& L = c.lv[l];
     LevelStruct& T = S.lv[l];
@@ -792,6 +857,7 @@ void load_struct(llg_ctx& c, const StructSet& S) {
   c.count = S.count;
   c.scan_tmp = S.scan_tmp;
   c.ops = S.ops;
+  c.build = S.build;
   for (int l = 0; l < LLG_MAX_LEVELS; ++l) {
     Level& L = c.lv[l];
     const LevelStruct& T = S.lv[l];
@@ -925,6 +991,9 @@ void allocate_numeric(llg_ctx& c, Arena& ar) {
   else
     plan_tail<double>(c, c.ta64);
   c.team_st = (TeamState*)ar.get(sizeof(TeamState), true);
+  c.build_st = (TeamState*)ar.get(sizeof(TeamState), true);
+  c.build = ar.get(LLG_MAX_LEVELS * sizeof(BuildLevel), true);
+  if (overlapped_rebuild(c.opts)) c.build2 = ar.get(LLG_MAX_LEVELS * sizeof(BuildLevel), true);
   const size_t op = f32 ? sizeof(TeamOp<float>) : sizeof(TeamOp<double>);
   const size_t list = TEAM_OPS * op + TEAM_TOUCH * sizeof(TeamTouch);
   c.ops = ar.get(list, true);
@@ -1312,6 +1381,7 @@ void rebuild_overlapped(llg_ctx& c) {
   ar.st = c.aux;
   ar.flag_word = 1;
   ar.keep_grid = true;
+  ar.team_from = c.build_from;
   try {
     (void)build_structure(c, ar);
   } catch (...) {
@@ -1345,6 +1415,7 @@ void setup_values(llg_ctx& c, const double* m, const double* mprev, const double
     ar.ptrs = &c.ptrs;
     ar.st = st;
     ar.keep_grid = true;
+    ar.team_from = c.build_from;
     (void)build_structure(c, ar);
   }
   Level& L0 = c.lv[0];
@@ -2311,11 +2382,22 @@ llg_status llg_create(const llg_grid* grid, const llg_opts* opts, void* d_worksp
     ar.base = c->ws;
     ar.cap = bytes;
     ar.st = c->st;
+    std::vector<BuildLevel> lists;
+    ar.rec = &lists;
     c->L = build_structure(*c, ar);
     allocate_numeric(*c, ar);
     c->used = ar.off;
     launch_fill_i32(c->st, (int32_t*)c->team_st, sizeof(TeamState) / sizeof(int32_t), 0);
+    launch_fill_i32(c->st, (int32_t*)c->build_st, sizeof(TeamState) / sizeof(int32_t), 0);
     LCHK();
+    c->nbuild = (int)lists.size();
+    auto put_lists = [&](void* dev) {
+      c->build = dev;
+      if (lists.empty()) return;
+      HIPX(hipMemcpyAsync(dev, lists.data(), lists.size() * sizeof(BuildLevel), hipMemcpyHostToDevice, c->st));
+      HIPX(hipStreamSynchronize(c->st));
+    };
+    put_lists(c->build);
     static std::atomic<unsigned> contexts{0};  // contexts take the XCDs in turn
     c->team_xcd = (int)(contexts.fetch_add(1, std::memory_order_relaxed) % 8);
     void* ops1 = c->ops;
@@ -2332,8 +2414,11 @@ llg_status llg_create(const llg_grid* grid, const llg_opts* opts, void* d_worksp
       a2.base = c->ws + c->used;
       a2.cap = bytes - c->used;
       a2.st = c->st;
+      lists.clear();
+      a2.rec = &lists;
       (void)build_structure(*c, a2);
       c->used += a2.off;
+      put_lists(c->build2);
       plan_team(*c, c->ops2);
       save_struct(*c, c->sets[1]);
       HIPX(hipMemcpyAsync(c->hflags, c->flags, sizeof(int32_t), hipMemcpyDeviceToHost, c->st));

@@ -7,6 +7,7 @@
 #include <algorithm>
 
 #include "llg_internal.h"
+#include "team.h"
 
 namespace llg {
 
@@ -330,32 +331,32 @@ __device__ inline bool key_before_h(const EdgeKey& a, uint64_t& ha, bool& hav, c
 // slots [kb, k1) that lane sub of its G lanes visits (every G-th slot); best
 // and bk are updated in place.  Neighbours are examined U at a time so
 // that their loads are in flight together.
-template <int G, int U = 4>
-__device__ inline void row_best(int64_t i, int sub, int32_t mxi, int32_t kb, int32_t k1,
-                                const int32_t* __restrict__ gci, const int32_t* __restrict__ gw,
-                                const NodeSt* __restrict__ ns, uint64_t salt, int32_t bnum, int32_t bden,
-                                int32_t& best, EdgeKey& bk) {
-  const uint64_t ri = node_rank(i, salt);
+// rec(j): node j's record; rank(j): its visiting rank; ci(k), wt(k): column
+// and weight of slot k.
+template <int G, int U, typename REC, typename RANK, typename CI, typename WT>
+__device__ inline void row_best_of(int64_t i, int sub, int32_t mxi, int32_t kb, int32_t k1, CI ci, WT wt, REC rec,
+                                   RANK rank, uint64_t salt, int32_t bnum, int32_t bden, int32_t& best, EdgeKey& bk) {
+  const uint64_t ri = rank(i);
   for (int32_t k0 = kb + sub; k0 < k1; k0 += U * G) {
     int32_t jj[U], ww[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bool ok = k0 + u * G < k1;
-      jj[u] = ok ? gci[k0 + u * G] : -1;
-      ww[u] = ok ? gw[k0 + u * G] : 0;
+      jj[u] = ok ? ci(k0 + u * G) : -1;
+      ww[u] = ok ? wt(k0 + u * G) : 0;
     }
     // the candidates' records, all U loads issued together (a padding
     // slot reads node i's own record and is masked)
     NodeSt sj[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) sj[u] = ns[jj[u] >= 0 ? jj[u] : i];
+    for (int u = 0; u < U; ++u) sj[u] = rec(jj[u] >= 0 ? jj[u] : i);
     bool fr[U];
     uint64_t rr[U];
     int32_t mj[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       fr[u] = jj[u] >= 0 && sj[u].mate < 0;
-      rr[u] = node_rank(jj[u] >= 0 ? jj[u] : i, salt);
+      rr[u] = rank(jj[u] >= 0 ? jj[u] : i);
       mj[u] = sj[u].mx;
     }
 #pragma unroll
@@ -378,6 +379,16 @@ __device__ inline void row_best(int64_t i, int sub, int32_t mxi, int32_t kb, int
       }
     }
   }
+}
+
+template <int G, int U = 4>
+__device__ inline void row_best(int64_t i, int sub, int32_t mxi, int32_t kb, int32_t k1,
+                                const int32_t* __restrict__ gci, const int32_t* __restrict__ gw,
+                                const NodeSt* __restrict__ ns, uint64_t salt, int32_t bnum, int32_t bden,
+                                int32_t& best, EdgeKey& bk) {
+  row_best_of<G, U>(
+      i, sub, mxi, kb, k1, [&](int32_t k) { return gci[k]; }, [&](int32_t k) { return gw[k]; },
+      [&](int64_t j) { return ns[j]; }, [&](int64_t j) { return node_rank(j, salt); }, salt, bnum, bden, best, bk);
 }
 
 // One handshake round: every free node proposes its earliest candidate edge
@@ -800,13 +811,9 @@ __global__ void k_cg_count(int64_t nc, const int32_t* lead, const int32_t* mate,
 // contiguous loads and stores and turns nrp into the row pointers.
 // The entries of row I in ascending column order, for a row of more than T
 // candidates: with emit, written at out/ow; returns their number.
-__device__ int32_t cg_row_select(int32_t I, int32_t ka, int32_t na, int32_t kb, int32_t nb,
-                                 const int32_t* __restrict__ gci, const int32_t* __restrict__ gw,
-                                 const int32_t* __restrict__ agg, bool emit, int32_t* out, int32_t* ow,
+template <typename COL, typename WGT>
+__device__ int32_t cg_row_select(int32_t I, int32_t c, COL col, WGT wgt, bool emit, int32_t* out, int32_t* ow,
                                  int32_t* mx) {
-  const int32_t c = na + nb;
-  auto col = [&](int32_t e) { return agg[gci[e < na ? ka + e : kb + (e - na)]]; };
-  auto wgt = [&](int32_t e) { return gw[e < na ? ka + e : kb + (e - na)]; };
   int32_t u = 0, last = -1;
   for (;;) {
     int32_t m = 0x7fffffff, w = 0;
@@ -934,8 +941,10 @@ __global__ void __launch_bounds__(TPB) k_cg_fill(int64_t nc, const int32_t* __re
   for (int q = 0; q < PS; ++q)
     if (kk[q] != -1) ent[pos++] = make_int2(kk[q], ww[q]);
   int32_t mx = 0;  // the row's largest weight
+  auto colf = [&](int32_t e) { return agg[gci[e < na ? ka + e : kb + (e - na)]]; };
+  auto wgtf = [&](int32_t e) { return gw[e < na ? ka + e : kb + (e - na)]; };
   if (!small) {
-    if (I < nc && lane == 0) u = cg_row_select((int32_t)I, ka, na, kb, nb, gci, gw, agg, false, nullptr, nullptr, &mx);
+    if (I < nc && lane == 0) u = cg_row_select((int32_t)I, c, colf, wgtf, false, nullptr, nullptr, &mx);
     u = __shfl(u, 0, G);
   }
   if (I >= nc) u = 0;
@@ -967,7 +976,7 @@ __global__ void __launch_bounds__(TPB) k_cg_fill(int64_t nc, const int32_t* __re
         mx = max(mx, v.y);
       }
     } else if (lane == 0) {
-      (void)cg_row_select((int32_t)I, ka, na, kb, nb, gci, gw, agg, true, cj + o, cw + o, &mx);
+      (void)cg_row_select((int32_t)I, c, colf, wgtf, true, cj + o, cw + o, &mx);
     }
     if (lane == 0) nrp[I] = s_off[r];
   }
@@ -1010,7 +1019,13 @@ struct PassMaps {
   const int32_t* mate[MAX_PASS];
 };
 
-template <int NP>
+struct PlainLd {
+  __device__ int32_t operator()(const int32_t* p) const { return *p; }
+};
+struct TeamLd {
+  __device__ int32_t operator()(const int32_t* p) const { return team_ld(p); }
+};
+template <int NP, typename LD = PlainLd>
 __device__ inline int expand_members(int32_t I, const PassMaps& pm, int32_t (&m)[1 << NP]) {
   m[0] = I;
 #pragma unroll
@@ -1022,8 +1037,8 @@ __device__ inline int expand_members(int32_t I, const PassMaps& pm, int32_t (&m)
       const int32_t A = m[x];
       int32_t L = -1, M = -1;
       if (A >= 0) {
-        L = pm.lead[q][A];
-        const int32_t mm = pm.mate[q][L];
+        L = LD()(pm.lead[q] + A);
+        const int32_t mm = LD()(pm.mate[q] + L);
         M = mm >= 0 ? mm : -1;
       }
       m[2 * x] = L;
@@ -1078,6 +1093,657 @@ __global__ void k_member_fill(int64_t nc, PassMaps pm, const int32_t* mptr, int3
       acc[m[x]] = (int32_t)I;
     }
   }
+}
+
+// ------------------------------------------------ small levels by a team
+// The structure of the small levels (matching passes, coarse graphs, member
+// lists, block patterns) in one launch of a team: 30 to 60 launches a level
+// otherwise, each of 2.5-5 us whatever the level's size.  A member keeps a
+// contiguous range of a pass's nodes, of its aggregates and of the next
+// level's slices, so the scans need the members' totals only.  Everything
+// written in the launch is read by team_ld.  Decisions and orders are those
+// of the per-pass kernels, so the structure is the same.
+// Bound by latency: a matching round is two barriers and the walk of the
+// rows still free (4 us in 2D, 5-19 us at 21k nodes in 3D), a scan a barrier
+// (3 us), a level's end 8-17 us.  Steps with a level's kernels one by one ->
+// with the team: 64^2 3.93 -> 3.30 ms, 603 x 411 8.74 -> 8.23, 1024^2 23.9 ->
+// 23.2, 131 x 75 x 97 7.00 -> 6.75, 41^3 3.27 -> 3.14 ms.
+struct TeamRange {
+  int32_t lo, hi;
+};
+__device__ inline TeamRange team_range(const Team& t, int32_t n, int32_t unit = 1) {
+  const int32_t units = (n + unit - 1) / unit;
+  const int32_t per = (units + (int32_t)t.n - 1) / (int32_t)t.n;
+  return TeamRange{min(n, (int32_t)t.rank * per * unit), min(n, ((int32_t)t.rank + 1) * per * unit)};
+}
+
+// Exclusive scan of one value per thread over the workgroup; *total: the sum.
+template <int NT>
+__device__ inline int32_t wg_scan(int32_t v, int32_t* sh, int32_t* total) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int32_t incl = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t y = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += y;
+  }
+  __syncthreads();
+  if (lane == 63) sh[wv] = incl;
+  __syncthreads();
+  int32_t before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) {
+    const int32_t x = sh[w];
+    before += w < wv ? x : 0;
+    all += x;
+  }
+  *total = all;
+  return before + incl - v;
+}
+
+// Sum of v over the workgroup, the same on every thread.
+template <int NT>
+__device__ inline int32_t wg_total(int32_t v, int32_t* sh) {
+  int32_t all;
+  (void)wg_scan<NT>(v, sh, &all);
+  return all;
+}
+
+// The members' totals: publish one, then (after a barrier) the sum before
+// this member's and that of all.
+__device__ inline void team_publish(const Team& t, int slot, int32_t v) {
+  if (threadIdx.x == 0)
+    __hip_atomic_store(&t.s->sum[slot][t.rank], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ inline int32_t team_before(const Team& t, int slot, int32_t* total) {
+  const int lane = threadIdx.x & 63;
+  int32_t v = lane < (int)t.n ? team_ld(&t.s->sum[slot][lane]) : 0;
+  int32_t b = lane < (int)t.rank ? v : 0;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    v += __shfl_xor(v, off, 64);
+    b += __shfl_xor(b, off, 64);
+  }
+  *total = v;
+  return b;
+}
+
+__device__ inline NodeSt team_record(const NodeSt* ns, int64_t j) {
+  const uint64_t v = team_ld((const uint64_t*)(ns + j));
+  NodeSt r;
+  __builtin_memcpy(&r, &v, sizeof(r));
+  return r;
+}
+
+// The key of a candidate edge with the upper half of the visiting rank (read
+// from P.id, which is free until the numbering) and the edge hash taken once
+// and only on a tie: a walk is bound by its 64-bit multiplies, a quarter of
+// the full rate.  Equal upper halves are compared in full.
+struct TeamKey {
+  uint32_t rank;
+  int32_t first, w, lo, hi;
+  uint64_t hash;
+  bool hashed;
+};
+__device__ inline bool team_key_before(TeamKey& a, TeamKey& b, uint64_t salt) {
+  if (a.first != b.first) {
+    if (a.rank != b.rank) return a.rank < b.rank;
+    const uint64_t ra = node_rank(a.first, salt), rb = node_rank(b.first, salt);
+    return ra != rb ? ra < rb : a.first < b.first;
+  }
+  if (a.w != b.w) return a.w > b.w;
+  if (!a.hashed) {
+    a.hash = edge_hash(a.lo, a.hi, salt);
+    a.hashed = true;
+  }
+  if (!b.hashed) {
+    b.hash = edge_hash(b.lo, b.hi, salt);
+    b.hashed = true;
+  }
+  if (a.hash != b.hash) return a.hash > b.hash;
+  if (a.lo != b.lo) return a.lo < b.lo;
+  return a.hi < b.hi;
+}
+
+// Walkers w < nw listed in LDS (list(w): node, largest weight, row), PK_G
+// lanes each; rec(j) and rank(j): record and upper rank of a node; done(i,
+// best) on a walker's first lane.
+template <int NT, typename LIST, typename REC, typename RANK, typename DONE>
+__device__ inline void team_walk(int nw, LIST list, const BuildPass& P, REC rec, RANK rank, int32_t bnum,
+                                 int32_t bden, DONE done) {
+  const int sub = (int)threadIdx.x % PK_G;
+  for (int t0 = 0; t0 < nw; t0 += NT / PK_G) {
+    const int w = t0 + (int)threadIdx.x / PK_G;
+    const bool act = w < nw;
+    const int4 wk = act ? list(w) : make_int4(0, 0, 0, 0);
+    const int32_t i = wk.x;
+    const uint32_t ri = act ? rank(i) : 0;
+    int32_t best = -1;
+    TeamKey bk{};
+    for (int32_t k0 = wk.z + sub; k0 < wk.w; k0 += PK_U * PK_G) {  // no row without a walker
+      int32_t jj[PK_U], ww[PK_U];
+      NodeSt sj[PK_U];
+      uint32_t rr[PK_U];
+#pragma unroll
+      for (int u = 0; u < PK_U; ++u) {
+        const bool ok = k0 + u * PK_G < wk.w;
+        jj[u] = ok ? team_ld(P.cci + k0 + u * PK_G) : -1;
+        ww[u] = ok ? team_ld(P.cw + k0 + u * PK_G) : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < PK_U; ++u) {
+        const int32_t j = jj[u] >= 0 ? jj[u] : i;
+        sj[u] = rec(j);
+        rr[u] = rank(j);
+      }
+#pragma unroll
+      for (int u = 0; u < PK_U; ++u) {
+        if (jj[u] < 0 || sj[u].mate >= 0) continue;
+        const int32_t j = jj[u], wt = ww[u];
+        bool ifirst = ri < rr[u];
+        if (ri == rr[u]) {
+          const uint64_t x = node_rank(i, P.salt), y = node_rank(j, P.salt);
+          ifirst = x != y ? x < y : i < j;
+        }
+        const int32_t mf = ifirst ? wk.y : sj[u].mx;
+        if ((int64_t)bden * wt < (int64_t)bnum * mf) continue;
+        TeamKey e{ifirst ? ri : rr[u], ifirst ? i : j, wt, min(i, j), max(i, j), 0, false};
+        if (best < 0 || team_key_before(e, bk, P.salt)) {
+          bk = e;
+          best = j;
+        }
+      }
+    }
+#pragma unroll
+    for (int off = 1; off < PK_G; off <<= 1) {
+      TeamKey o;
+      const int32_t ob = __shfl_xor(best, off, PK_G);
+      o.rank = __shfl_xor(bk.rank, off, PK_G);
+      o.first = __shfl_xor(bk.first, off, PK_G);
+      o.w = __shfl_xor(bk.w, off, PK_G);
+      o.lo = __shfl_xor(bk.lo, off, PK_G);
+      o.hi = __shfl_xor(bk.hi, off, PK_G);
+      o.hash = __shfl_xor(bk.hash, off, PK_G);
+      o.hashed = __shfl_xor((int)bk.hashed, off, PK_G) != 0;
+      if (ob >= 0 && (best < 0 || team_key_before(o, bk, P.salt))) {
+        bk = o;
+        best = ob;
+      }
+    }
+    if (act && sub == 0) done(i, best);
+  }
+}
+
+// Every handshake round of a pass by the team, two barriers a round; false
+// when a pass of n nodes takes more than n rounds (the same on every member).
+template <int NT>
+__device__ inline bool team_match(Team& t, const BuildPass& P, int32_t bnum, int32_t bden, unsigned char* lds) {
+  int4* walk = (int4*)lds;  // one per thread
+  int* nwp = (int*)(walk + NT);
+  const TeamRange R = team_range(t, P.cn);
+  const int tid = (int)threadIdx.x;
+  for (int32_t i = R.lo + tid; i < R.hi; i += NT) P.id[i] = (int32_t)(node_rank(i, P.salt) >> 32);
+  t.barrier();
+  auto rec = [&](int64_t j) { return team_record(P.ns, j); };
+  auto rank = [&](int64_t j) { return (uint32_t)team_ld(P.id + j); };
+  for (int32_t r = 0;; ++r) {
+    bool any = false;
+    for (int32_t i0 = R.lo; i0 < R.hi; i0 += NT) {
+      if (tid == 0) *nwp = 0;
+      __syncthreads();
+      const int32_t i = i0 + tid;
+      if (i < R.hi) {
+        const int32_t mi = team_ld(P.mate + i), pj = team_ld(P.prop + i);
+        if (mi >= 0 && pj >= 0) P.prop[i] = -1;
+        if (mi == -1) {
+          const NodeSt si = rec(i);
+          const int32_t kb = team_ld(P.crp + i), k1 = team_ld(P.crp + i + 1);
+          if (pj >= 0 && team_ld(P.mate + pj) < 0)
+            any = true;
+          else
+            walk[atomicAdd(nwp, 1)] = make_int4(i, si.mx, kb, k1);
+        }
+      }
+      __syncthreads();
+      team_walk<NT>(*nwp, [&](int w) { return walk[w]; }, P, rec, rank, bnum, bden, [&](int32_t w, int32_t best) {
+        P.prop[w] = best;
+        if (best < 0) P.mate[w] = -2;
+        any = any || best >= 0;
+      });
+      __syncthreads();
+    }
+    const int mine = __syncthreads_or(any);
+    team_publish(t, 0, mine ? 1 : 0);
+    t.barrier();
+    int32_t all;
+    (void)team_before(t, 0, &all);
+    if (all == 0) return true;
+    if (r > P.cn) return false;
+    for (int32_t i = R.lo + tid; i < R.hi; i += NT) {
+      const int32_t p = team_ld(P.prop + i);
+      if (p >= 0 && team_ld(P.prop + p) == i) {
+        P.mate[i] = p;
+        P.ns[i].mate = p;
+      }
+    }
+    t.barrier();
+  }
+}
+
+// The same by one member with the pass's state in LDS (passes of at most
+// BUILD_LDS nodes): a round costs its walkers' rows and workgroup barriers,
+// 2-4 us against 4-5 us by the team.
+template <int NT>
+__device__ inline bool wg_match(const BuildPass& P, int32_t bnum, int32_t bden, unsigned char* lds) {
+  uint32_t* rk = (uint32_t*)lds;
+  int32_t* mate = (int32_t*)(rk + BUILD_LDS);
+  int32_t* prop = mate + BUILD_LDS;
+  int32_t* mx = prop + BUILD_LDS;
+  int32_t* list = mx + BUILD_LDS;
+  int* nwp = list + BUILD_LDS;
+  const int tid = (int)threadIdx.x;
+  const int32_t n = P.cn;
+  for (int32_t i = tid; i < n; i += NT) {
+    rk[i] = (uint32_t)(node_rank(i, P.salt) >> 32);
+    mate[i] = -1;
+    prop[i] = -1;
+    mx[i] = team_record(P.ns, i).mx;
+  }
+  auto rec = [&](int64_t j) { return NodeSt{mx[j], mate[j]}; };
+  auto rank = [&](int64_t j) { return rk[j]; };
+  bool ok = true;
+  for (int32_t r = 0;; ++r) {
+    if (tid == 0) *nwp = 0;
+    __syncthreads();
+    bool any = false;
+    for (int32_t i = tid; i < n; i += NT) {
+      const int32_t mi = mate[i], pj = prop[i];
+      if (mi >= 0 && pj >= 0) prop[i] = -1;
+      if (mi == -1) {
+        if (pj >= 0 && mate[pj] < 0)
+          any = true;
+        else
+          list[atomicAdd(nwp, 1)] = i;
+      }
+    }
+    __syncthreads();
+    team_walk<NT>(*nwp,
+                  [&](int w) {
+                    const int32_t i = list[w];
+                    return make_int4(i, mx[i], team_ld(P.crp + i), team_ld(P.crp + i + 1));
+                  },
+                  P, rec, rank, bnum, bden, [&](int32_t w, int32_t best) {
+                    prop[w] = best;
+                    if (best < 0) mate[w] = -2;
+                    any = any || best >= 0;
+                  });
+    if (!__syncthreads_or(any)) break;
+    if (r > n) {
+      ok = false;
+      break;
+    }
+    for (int32_t i = tid; i < n; i += NT) {
+      const int32_t p = prop[i];
+      if (p >= 0 && prop[p] == i) mate[i] = p;
+    }
+    __syncthreads();
+  }
+  for (int32_t i = tid; i < n; i += NT) P.mate[i] = mate[i];
+  return ok;
+}
+
+// A pass after its matching: numbering, coarse rows, coarse graph.  False (on
+// every member) when a count is not the plan's: nothing is written past the
+// planned buffers, and the checks of the counts report it.
+template <int NT>
+__device__ inline bool team_pass(Team& t, const BuildPass& P, unsigned char* lds, int32_t* sh) {
+  const int tid = (int)threadIdx.x;
+  const TeamRange R = team_range(t, P.cn);
+  // leaders, numbered in ascending order; a leader writes its mate's number
+  auto leads = [&](int32_t i, int32_t& m) {
+    m = i < R.hi ? team_ld(P.mate + i) : 0;
+    return i < R.hi && (m < 0 || i < m);
+  };
+  int32_t c = 0, m;
+  for (int32_t i = R.lo + tid; i < R.hi; i += NT) c += leads(i, m) ? 1 : 0;
+  team_publish(t, 1, wg_total<NT>(c, sh));
+  t.barrier();
+  int32_t nc;
+  int32_t run = team_before(t, 1, &nc);
+  for (int32_t i0 = R.lo; i0 < R.hi; i0 += NT) {
+    const int32_t i = i0 + tid;
+    const bool l = leads(i, m);
+    int32_t all;
+    const int32_t a = run + wg_scan<NT>(l ? 1 : 0, sh, &all);
+    if (l && a < P.nc) {
+      P.agg[i] = a;
+      P.lead[a] = i;
+      if (m >= 0) P.agg[m] = a;
+    }
+    run += all;
+  }
+  if (t.rank == 0 && tid == 0) P.id[P.cn] = nc;
+  t.barrier();
+  if (nc != P.nc) return false;
+  // room for the candidates of every coarse row
+  const TeamRange C = team_range(t, nc);
+  auto cand = [&](int32_t I) {
+    const int32_t a = team_ld(P.lead + I), b = team_ld(P.mate + a);
+    int32_t k = team_ld(P.crp + a + 1) - team_ld(P.crp + a);
+    if (b >= 0) k += team_ld(P.crp + b + 1) - team_ld(P.crp + b);
+    return k;
+  };
+  c = 0;
+  for (int32_t I = C.lo + tid; I < C.hi; I += NT) c += cand(I);
+  team_publish(t, 2, wg_total<NT>(c, sh));
+  t.barrier();
+  int32_t ncand;
+  run = team_before(t, 2, &ncand);
+  if (t.rank == 0 && tid == 0) P.cnt[nc] = ncand;
+  if (ncand != P.ncand) return false;
+  for (int32_t I0 = C.lo; I0 < C.hi; I0 += NT) {
+    const int32_t I = I0 + tid;
+    int32_t all;
+    const int32_t o = run + wg_scan<NT>(I < C.hi ? cand(I) : 0, sh, &all);
+    if (I < C.hi) P.cnt[I] = o;
+    run += all;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  // rows through a table in LDS as in k_cg_fill, 16 lanes and 64 slots a row
+  constexpr int G = 16, T = 64, PS = T / G, RW = NT / G;
+  int32_t* s_key = (int32_t*)lds;
+  int32_t* s_wt = s_key + RW * T;
+  int2* s_ent = (int2*)(s_wt + RW * T);
+  const int r = tid / G, lane = tid % G;
+  int32_t* key = s_key + r * T;
+  int32_t* wt = s_wt + r * T;
+  int2* ent = s_ent + r * T;
+  int32_t mylen = 0;
+  for (int32_t I0 = C.lo; I0 < C.hi; I0 += RW) {
+    const int32_t I = I0 + r;
+    const bool in = I < C.hi;
+#pragma unroll
+    for (int q = 0; q < PS; ++q) {
+      key[lane * PS + q] = -1;
+      wt[lane * PS + q] = 0;
+    }
+    int32_t ka = 0, na = 0, kb = 0, nb = 0, o = 0;
+    if (in) {
+      const int32_t a = team_ld(P.lead + I), b = team_ld(P.mate + a);
+      ka = team_ld(P.crp + a);
+      na = team_ld(P.crp + a + 1) - ka;
+      if (b >= 0) {
+        kb = team_ld(P.crp + b);
+        nb = team_ld(P.crp + b + 1) - kb;
+      }
+      o = team_ld(P.cnt + I);
+    }
+    const int32_t n = na + nb;
+    const bool small = in && n <= T;
+    auto at = [&](int32_t e) { return e < na ? ka + e : kb + (e - na); };
+    auto colf = [&](int32_t e) { return team_ld(P.agg + team_ld(P.cci + at(e))); };
+    auto wgtf = [&](int32_t e) { return team_ld(P.cw + at(e)); };
+    __syncthreads();
+    if (small) {
+      for (int32_t e = lane; e < n; e += G) {
+        const int32_t J = colf(e), w = wgtf(e);
+        if (J == I) continue;
+        unsigned h = ((unsigned)J * 0x9E3779B1u) >> (32 - __builtin_ctz(T));
+        for (;;) {  // at most n <= T distinct columns: a free slot or J's own is found
+          const int32_t old = atomicCAS(&key[h], -1, J);
+          if (old == -1 || old == J) {
+            atomicAdd(&wt[h], w);
+            break;
+          }
+          h = (h + 1) & (T - 1);
+        }
+      }
+    }
+    __syncthreads();
+    int32_t kk[PS], ww[PS];
+    int cl = 0;
+#pragma unroll
+    for (int q = 0; q < PS; ++q) {
+      kk[q] = key[lane * PS + q];
+      ww[q] = wt[lane * PS + q];
+      cl += kk[q] != -1;
+    }
+    int incl = cl;
+#pragma unroll
+    for (int off = 1; off < G; off <<= 1) {
+      const int v = __shfl_up(incl, off, G);
+      if (lane >= off) incl += v;
+    }
+    int32_t u = __shfl(incl, G - 1, G);
+    int pos = incl - cl;
+#pragma unroll
+    for (int q = 0; q < PS; ++q)
+      if (kk[q] != -1) ent[pos++] = make_int2(kk[q], ww[q]);
+    __syncthreads();
+    int32_t mx = 0;
+    if (small) {
+      for (int e = lane; e < u; e += G) {
+        const int2 v = ent[e];
+        int rk = 0;
+        for (int x = 0; x < u; ++x) rk += ent[x].x < v.x;
+        P.cj[o + rk] = v.x;
+        P.cwt[o + rk] = v.y;
+        mx = max(mx, v.y);
+      }
+    } else {
+      u = in && lane == 0 ? cg_row_select(I, n, colf, wgtf, true, P.cj + o, P.cwt + o, &mx) : 0;
+      u = __shfl(u, 0, G);
+    }
+#pragma unroll
+    for (int off = 1; off < G; off <<= 1) mx = max(mx, __shfl_xor(mx, off, G));
+    if (in && lane == 0) {
+      P.nrp[I] = u;  // the row's length for now
+      P.ns2[I] = NodeSt{mx, -1};
+      P.mate2[I] = -1;
+      P.prop2[I] = -1;
+      mylen += u;
+    }
+  }
+  team_publish(t, 3, wg_total<NT>(mylen, sh));
+  t.barrier();
+  int32_t ng;
+  run = team_before(t, 3, &ng);
+  if (t.rank == 0 && tid == 0) {
+    *P.ngp = ng;
+    P.nrp[nc] = ng;
+  }
+  if (ng != P.ng) return false;
+  {
+    int32_t* s_src = (int32_t*)lds;
+    int32_t* s_dst = s_src + NT;
+    int32_t* s_len = s_dst + NT;
+    for (int32_t I0 = C.lo; I0 < C.hi; I0 += NT) {
+      const int32_t I = I0 + tid;
+      int32_t all;
+      const int32_t len = I < C.hi ? team_ld(P.nrp + I) : 0;
+      const int32_t d = run + wg_scan<NT>(len, sh, &all);
+      if (I < C.hi) P.nrp[I] = d;
+      s_src[tid] = I < C.hi ? team_ld(P.cnt + I) : 0;
+      s_dst[tid] = d;
+      s_len[tid] = len;
+      run += all;
+      __syncthreads();
+      // 16 lanes a row, four rows at a time with their loads in flight together
+      for (int q0 = tid / 16; q0 < min(NT, C.hi - I0); q0 += 4 * (NT / 16)) {
+        int32_t len[4], most = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int q = q0 + u * (NT / 16);
+          len[u] = q < NT ? s_len[q] : 0;
+          most = max(most, len[u]);
+        }
+        for (int e = tid % 16; e < most; e += 16) {
+          int32_t cc[4], cv[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int q = q0 + u * (NT / 16);
+            cc[u] = e < len[u] ? team_ld(P.cj + s_src[q] + e) : 0;
+            cv[u] = e < len[u] ? team_ld(P.cwt + s_src[q] + e) : 0;
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int q = q0 + u * (NT / 16);
+            if (e < len[u]) {
+              P.nci[s_dst[q] + e] = cc[u];
+              P.nw[s_dst[q] + e] = cv[u];
+            }
+          }
+        }
+      }
+      __syncthreads();
+    }
+  }
+  t.barrier();
+  return true;
+}
+
+// Members of the composite aggregates and the next level's block pattern.
+template <int NT, int NP>
+__device__ inline bool team_level(Team& t, const BuildLevel& L, int32_t* sh) {
+  const int tid = (int)threadIdx.x;
+  PassMaps pm{};
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    pm.lead[q] = L.pass[q].lead;
+    pm.mate[q] = L.pass[q].mate;
+  }
+  const TeamRange C = team_range(t, L.nc);
+  const TeamRange S = team_range(t, L.nc, SL);  // rows of the next level, whole slices
+  int32_t m[1 << NP], c = 0;
+  for (int32_t I = C.lo + tid; I < C.hi; I += NT) c += expand_members<NP, TeamLd>(I, pm, m);
+  team_publish(t, 1, wg_total<NT>(c, sh));
+  // the pattern's rows meanwhile: the graph row with the diagonal in column order
+  for (int32_t i = S.lo + tid; i < S.hi; i += NT) L.brp[i] = team_ld(L.grp + i) + i;
+  if (S.hi == L.nc && S.lo < S.hi && tid == 0) L.brp[L.nc] = team_ld(L.grp + L.nc) + L.nc;
+  int32_t slots = 0;
+  for (int32_t i0 = S.lo; i0 < S.hi; i0 += NT / PC_L) {
+    const int32_t i = i0 + tid / PC_L, sub = tid % PC_L;
+    if (i >= S.hi) continue;
+    const int32_t k0 = team_ld(L.grp + i), k1 = team_ld(L.grp + i + 1), o = k0 + i;
+    for (int32_t k = k0 + sub; k < k1; k += PC_L) {
+      const int32_t col = team_ld(L.gci + k);
+      const bool after = col > i;
+      L.bci[o + (k - k0) + (after ? 1 : 0)] = col;
+      if (after && (k == k0 || team_ld(L.gci + k - 1) < i)) L.bci[o + (k - k0)] = i;
+    }
+    if (sub == 0 && (k1 == k0 || team_ld(L.gci + k1 - 1) < i)) L.bci[o + (k1 - k0)] = i;
+  }
+  // a wavefront takes a slice: its width is that of its longest row
+  const int lane = tid & 63, wv = tid >> 6;
+  for (int32_t s0 = S.lo; s0 < S.hi; s0 += NT) {
+    const int32_t i = s0 + tid;
+    int32_t w = i < S.hi ? team_ld(L.grp + i + 1) - team_ld(L.grp + i) + 1 : 0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) w = max(w, __shfl_xor(w, off, 64));
+    if (lane == 0 && i < S.hi) {
+      L.sl[i / SL] = w * SL;
+      slots += w * SL;
+    }
+  }
+  team_publish(t, 2, wg_total<NT>(slots, sh));
+  t.barrier();
+  int32_t tot;
+  int32_t run = team_before(t, 1, &tot);
+  if (t.rank == 0 && tid == 0) L.mptr[L.nc] = tot;
+  if (tot != L.n) return false;
+  for (int32_t I0 = C.lo; I0 < C.hi; I0 += NT) {
+    const int32_t I = I0 + tid;
+    const int32_t k = I < C.hi ? expand_members<NP, TeamLd>(I, pm, m) : 0;
+    int32_t all;
+    const int32_t o = run + wg_scan<NT>(k, sh, &all);
+    if (I < C.hi) {
+      L.mptr[I] = o;
+#pragma unroll
+      for (int x = 0; x < (1 << NP); ++x)
+        if (x < k) {
+          L.mem[o + x] = m[x];
+          L.acc[m[x]] = I;
+        }
+    }
+    run += all;
+  }
+  run = team_before(t, 2, &tot);
+  if (t.rank == 0 && tid == 0) L.sl[(L.nc + SL - 1) / SL] = tot;
+  if (tot != L.nslots) return false;
+  // slice pointers (a member has at most n / 64 / members slices: by one
+  // thread each in turns of the workgroup) and the columns of the slots
+  const int32_t s1 = S.lo < S.hi ? (S.hi + SL - 1) / SL : 0;  // no slice: an empty range
+  for (int32_t s0 = S.lo / SL; s0 < s1; s0 += NT) {
+    const int32_t s = s0 + tid;
+    const bool in = s < s1;
+    int32_t all;
+    const int32_t w = in ? team_ld(L.sl + s) : 0;
+    const int32_t o = run + wg_scan<NT>(w, sh, &all);
+    __syncthreads();
+    if (in) L.sl[s] = o;
+    run += all;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    for (int32_t q = wv; q < NT; q += NT / 64) {
+      const int32_t sq = s0 + q;
+      if (sq >= s1) break;
+      const int32_t base = team_ld(L.sl + sq);
+      const int32_t i = sq * SL + lane;
+      int32_t len = 0, r0 = 0;
+      if (i < L.nc) {
+        r0 = team_ld(L.grp + i) + i;
+        len = team_ld(L.grp + i + 1) + i + 1 - r0;
+      }
+      int32_t wd = len;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) wd = max(wd, __shfl_xor(wd, off, 64));
+      for (int32_t u = 0; u < wd; ++u) L.col[base + u * SL + lane] = u < len ? team_ld(L.bci + r0 + u) : -1;
+    }
+  }
+  return true;
+}
+
+template <int NT>
+__global__ void __launch_bounds__(NT) k_team_build(TeamState* ts, int pick, const BuildLevel* __restrict__ lv,
+                                                   int nlev, int npass, int32_t bnum, int32_t bden, int32_t* flag,
+                                                   int32_t bit) {
+  extern __shared__ __align__(16) unsigned char build_lds[];
+  __shared__ int32_t sh[NT / 64];
+  Team t;
+  if (!t.join(ts, (unsigned)pick)) return;
+  const int tid = (int)threadIdx.x;
+  bool ok = true;  // the same on every member
+  for (int l = 0; ok && l < nlev; ++l) {
+    const BuildLevel& L = lv[l];
+    for (int p = 0; ok && p < npass; ++p) {
+      const BuildPass& P = L.pass[p];
+      if (P.init) {  // the first pass of the list on a level nothing has set up
+        const TeamRange R = team_range(t, P.cn);
+        for (int32_t i = R.lo + tid; i < R.hi; i += NT) {
+          int32_t mx = 0;
+          for (int32_t k = P.crp[i]; k < P.crp[i + 1]; ++k) mx = max(mx, P.cw[k]);
+          P.ns[i] = NodeSt{mx, -1};
+          P.mate[i] = -1;
+          P.prop[i] = -1;
+        }
+        t.barrier();
+      }
+      bool done = true;
+      if (P.cn > BUILD_LDS) {
+        done = team_match<NT>(t, P, bnum, bden, build_lds);
+      } else {
+        if (t.rank == 0) done = wg_match<NT>(P, bnum, bden, build_lds);
+        t.barrier();
+      }
+      if (!done && t.rank == 0 && tid == 0) atomicOr(flag, bit);
+      ok = team_pass<NT>(t, P, build_lds, sh);
+    }
+    if (!ok || !L.next) continue;
+    ok = npass == 1 ? team_level<NT, 1>(t, L, sh) : npass == 2 ? team_level<NT, 2>(t, L, sh)
+                                                               : team_level<NT, 3>(t, L, sh);
+  }
+  t.leave();
 }
 
 // ---------------------------------------------------------------- colouring
@@ -2137,6 +2803,19 @@ __global__ void k_restrict_dense(int64_t nc, const int32_t* __restrict__ mptr, c
 }  // namespace
 
 // ---------------------------------------------------------------- launchers
+void launch_team_build(hipStream_t st, TeamState* ts, int pick, const BuildLevel* lv, int nlev, int npass,
+                       int32_t bnum, int32_t bden, int32_t* flag, int32_t bit, bool aside) {
+  // beside another stream's work with half the threads: the other half of
+  // the XCD's registers and wavefronts stays open to it (a full team holds
+  // up every kernel with a workgroup on that XCD for as long as it runs)
+  if (aside)
+    hipLaunchKernelGGL((k_team_build<512>), dim3(8 * TEAM_W), dim3(512), 512 / 16 * BUILD_LDS_ROW, st, ts, pick, lv,
+                       nlev, npass, bnum, bden, flag, bit);
+  else
+    hipLaunchKernelGGL((k_team_build<1024>), dim3(8 * TEAM_W), dim3(1024), 1024 / 16 * BUILD_LDS_ROW, st, ts, pick,
+                       lv, nlev, npass, bnum, bden, flag, bit);
+}
+
 void launch_fill_i32(hipStream_t st, int32_t* p, int64_t n, int32_t v) {
   if (n > 0) hipLaunchKernelGGL(k_fill_i32, dim3(nblk(n)), dim3(TPB), 0, st, p, n, v);
 }
@@ -2348,6 +3027,9 @@ template void launch_fact_blocks<float>(hipStream_t, int, int, int, double, cons
                                         float*);
 
 void init_kernel_attributes() {
+  // the team's tables take the default LDS limit whole, its static words come on top
+  (void)hipFuncSetAttribute((const void*)k_team_build<1024>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            1024 / 16 * BUILD_LDS_ROW);
   const size_t lds_max = (size_t)(GJ_LDS_MAX * GJ_LDS_MAX + 2 * GJ_LDS_MAX) * sizeof(double) +
                          GJ_LDS_MAX * sizeof(int32_t);
   (void)hipFuncSetAttribute((const void*)k_gauss_jordan_lds, hipFuncAttributeMaxDynamicSharedMemorySize,

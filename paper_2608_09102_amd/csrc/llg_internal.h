@@ -164,6 +164,49 @@ void launch_slice_width(hipStream_t st, int64_t n, const int32_t* rows, const in
 void launch_sell_cols(hipStream_t st, int64_t n, const int32_t* rows, const int32_t* brp, const int32_t* bci,
                       const int32_t* sl_ptr, int32_t* col);
 
+// prop[i] = proposed partner or -1; *any is set non-zero when some node proposes
+// Matching state of a node, one 8-byte record so that a candidate costs one
+// load: its largest edge weight and its mate (-1 while unmatched; the
+// proposal rounds mark a free node without candidates -2 in the mate array
+// only, which the record does not need to know).  The visiting rank is a
+// hash of the node's index, computed where it is compared (cheaper than the
+// 16-byte record that held it: 256^3 proposal rounds 13.3 -> 12.8 ms).
+struct alignas(8) NodeSt {
+  int32_t mx;
+  int32_t mate;
+};
+// The structure of the small levels in one launch of a team (see k_setup.hip):
+// per level its matching passes (from crp/cci/cw, cn nodes; nc aggregates,
+// ncand candidates and ng entries of the coarse graph by the plan), then the
+// members and the next level's pattern.
+struct BuildPass {
+  int32_t cn, nc, ncand, ng;
+  int64_t init;  // set up ns, mate and prop here
+  const int32_t *crp, *cci, *cw;
+  NodeSt* ns;
+  int32_t *mate, *prop, *id, *agg, *lead, *cnt, *cj, *cwt, *nrp, *nci, *nw, *ngp;
+  NodeSt* ns2;  // the next pass's state
+  int32_t *mate2, *prop2;
+  uint64_t salt;
+};
+struct BuildLevel {
+  BuildPass pass[MAX_PASS];
+  int32_t n, nc, nslots, next;  // next 0: the level coarsens too little, the passes were all
+  int32_t *mptr, *mem, *acc;
+  const int32_t *grp, *gci;         // the next level's graph
+  int32_t *brp, *bci, *sl, *col;    // and its block pattern
+};
+constexpr int BUILD_LDS = 640;       // largest pass matched by one member in LDS
+constexpr int BUILD_LDS_ROW = 1024;  // LDS of a row's table, 16 threads a row
+// The largest level built by a team: above it a pass has work for more than
+// one XCD.  A step with the line at 6144 / 24576 / 98304 nodes: 603 x 411
+// 8.39 / 8.28 / 8.64 ms, 1024^2 23.5 / 23.3 / 23.8, 131 x 75 x 97 6.79 / 6.74 /
+// 7.23, 41^3 3.04 / 3.09 / 3.46 ms.
+constexpr int64_t BUILD_NODES = 24576;
+struct TeamState;
+void launch_team_build(hipStream_t st, TeamState* ts, int pick, const BuildLevel* lv, int nlev, int npass,
+                       int32_t bnum, int32_t bden, int32_t* flag, int32_t bit, bool aside);
+
 // colour classes of the multicolour Gauss-Seidel smoother
 constexpr int MAX_COLOURS = 128;
 void launch_parity_colour(hipStream_t st, int nx, int ny, int nz, int32_t* col);
@@ -184,17 +227,6 @@ void launch_cls_gather(hipStream_t st, int64_t n, const int32_t* rows, Sell A, c
 
 // pairwise matching (one pass)
 void launch_node_rank(hipStream_t st, int64_t n, uint64_t salt, uint64_t* rank);
-// prop[i] = proposed partner or -1; *any is set non-zero when some node proposes
-// Matching state of a node, one 8-byte record so that a candidate costs one
-// load: its largest edge weight and its mate (-1 while unmatched; the
-// proposal rounds mark a free node without candidates -2 in the mate array
-// only, which the record does not need to know).  The visiting rank is a
-// hash of the node's index, computed where it is compared (cheaper than the
-// 16-byte record that held it: 256^3 proposal rounds 13.3 -> 12.8 ms).
-struct alignas(8) NodeSt {
-  int32_t mx;
-  int32_t mate;
-};
 // ns[i] = {max_k w_ik, -1}; mate[i] = -1; prop[i] = -1 (no proposal yet)
 void launch_match_init(hipStream_t st, int64_t n, const int32_t* grp, const int32_t* gw, uint64_t salt,
                        NodeSt* ns, int32_t* mate, int32_t* prop);

@@ -37,6 +37,9 @@ struct TeamState {
   unsigned left;  // candidates that have left
   unsigned pad2[31];
   unsigned flag[TEAM_W];  // barriers each member has reached
+  // totals the members publish for a scan, by slot (written again only after
+  // two barriers; not cleared)
+  int32_t sum[4][TEAM_W];
 };
 
 #if defined(__HIPCC__)
