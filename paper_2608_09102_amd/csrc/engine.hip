@@ -1435,8 +1435,9 @@ void setup_values(llg_ctx& c, const double* m, const double* mprev, const double
     LCHK();
   }
   if (field) {  // explicit field terms of the right-hand side (field 2: with the stray field)
-    if (field == 2) launch_stray(st, c.fd, m, mprev, c.nhat, c.fwork);
-    launch_field_rhs(st, c.N, c.prm, m, mprev, c.fd, field == 2 ? c.fwork : nullptr, c.b);
+    double* h = field == 2 ? stray_room(c.fd, c.fwork) : nullptr;
+    if (h) launch_stray(st, c.fd, m, mprev, c.nhat, c.fwork, h);
+    launch_field_rhs(st, c.N, c.prm, m, mprev, h, c.b);
     LCHK();
   }
   if (!amg) return;
@@ -2533,8 +2534,7 @@ llg_status llg_stray_field(llg_ctx* ctx, const double* d_m, double* d_h) {
   if (!ctx->opts.stray_field || !d_m || !d_h || !aligned8(d_m) || !aligned8(d_h)) return LLG_ERR_INVALID_ARG;
   return guard([&]() -> llg_status {
     demag_prepare(*ctx);
-    launch_stray(ctx->st, ctx->fd, d_m, nullptr, ctx->nhat, ctx->fwork);
-    launch_stray_out(ctx->st, ctx->fd, ctx->fwork, d_h);
+    launch_stray(ctx->st, ctx->fd, d_m, nullptr, ctx->nhat, ctx->fwork, d_h);
     LCHK();
     HIPX(hipStreamSynchronize(ctx->st));
     return LLG_OK;

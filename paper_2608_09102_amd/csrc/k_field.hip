@@ -7,16 +7,19 @@
 // Williams and Dunlop 1993; the point-dipole tensor beyond 16 cells), taken as
 // a cyclic convolution on the grid zero-padded to powers of two P >= 2n - 1
 // per axis.  The three real components travel as two complex planes
-// (m1 + i m2, m3); the forward transform reads only the n-box and skips the
-// lines that are zero, the product with the (real) transformed tensor
-// separates the packed pair by conjugate symmetry, and the inverse transform
-// writes only the n-box.  Line transforms are mixed-radix Stockham passes in
-// registers and LDS, several lines per workgroup.
+// (m1 + i m2, and the half of m3's that its conjugate symmetry leaves); the
+// forward transform reads the field itself and skips the lines that are zero,
+// the product with the (real) transformed tensor separates the packed pair by
+// conjugate symmetry, and the inverse transform writes h on the n-box.  The
+// last axis is taken there and back in one kernel with the product between.
+// Line transforms are mixed-radix Stockham passes in registers and LDS,
+// several lines per workgroup.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "llg.h"
 #include "llg_internal.h"
@@ -212,7 +215,7 @@ __device__ inline bool wrap(int64_t a, int64_t n, int64_t P, int64_t& off) {
 // for strided lines the C lines are adjacent in memory and lanes run across
 // them first, so that a row of C values is read together.
 struct FftPass {
-  int64_t n_inner, inner_stride, outer_stride, s, plane_stride;
+  int64_t n_inner, n_inner1, inner_stride, outer_stride, s, plane_stride;  // n_inner1: of plane 1
   int n_load, n_store, dir;
   double scale;
 };
@@ -260,108 +263,554 @@ __device__ inline void dft(double2* v, double dir) {
   }
 }
 
-// v[r] *= w^r, w = exp(i pi th), for r = 1..7
-__device__ inline void twiddle8(double2* v, double th) {
-  double s1, c1, s2, c2, s4, c4;
-  sincospi(th, &s1, &c1);
-  sincospi(2.0 * th, &s2, &c2);
-  sincospi(4.0 * th, &s4, &c4);
-  const double2 w1 = make_double2(c1, s1), w2 = make_double2(c2, s2), w4 = make_double2(c4, s4);
-  const double2 w3 = cmul(w1, w2);
-  v[1] = cmul(v[1], w1);
-  v[2] = cmul(v[2], w2);
-  v[3] = cmul(v[3], w3);
-  v[4] = cmul(v[4], w4);
-  v[5] = cmul(v[5], cmul(w1, w4));
-  v[6] = cmul(v[6], cmul(w2, w4));
-  v[7] = cmul(v[7], cmul(w3, w4));
+// exp(2 pi i k / 4096), filled with every tensor (the same values each time,
+// so streams may overlap).  Three loads replace three sincospi a pass, most of
+// its arithmetic: the last axis of 120 x 90 x 50 88 -> 80 us, 500^2's 45 -> 33.
+constexpr int FFT_MAX_BITS = 12;
+__device__ double2 fft_unit[1 << FFT_MAX_BITS];
+__global__ void k_fft_unit() {
+  const int k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (k >= 1 << FFT_MAX_BITS) return;
+  double s, c;
+  sincospi(2.0 * (double)k / (double)(1 << FFT_MAX_BITS), &s, &c);
+  fft_unit[k] = make_double2(c, s);
 }
 
-template <int BITS, bool CF>
-__global__ __launch_bounds__(512) void k_fft(double2* __restrict__ data, FftPass p) {
-  constexpr int L = 1 << BITS;
-  constexpr int T = L >= 8 ? L / 8 : 1;  // threads per line
-  constexpr int NR = L >= 8 ? 8 : L;     // values per thread
-  constexpr int C = 512 / T;             // lines per workgroup
-  constexpr int R0 = (BITS % 3 == 0) ? 8 : (1 << (BITS % 3));
-  constexpr int NMID = BITS > 3 ? (BITS - (R0 == 8 ? 3 : BITS % 3)) / 3 - 1 : -1;  // radix-8 passes between
-  constexpr int LP = L + (L >> 3);       // padded line in LDS
-  __shared__ double2 sm[L >= 16 ? C * LP : 1];
+// w[r - 1] = exp(dir 2 pi i k r / 2^bits) for r = 1..7, k < 2^bits / 8
+__device__ inline void twiddles8(double2* w, double dir, int k, int bits) {
+  k <<= FFT_MAX_BITS - bits;
+  w[0] = fft_unit[k];
+  w[1] = fft_unit[2 * k];
+  w[3] = fft_unit[4 * k];
+  w[0].y *= dir;
+  w[1].y *= dir;
+  w[3].y *= dir;
+  w[2] = cmul(w[0], w[1]);
+  w[4] = cmul(w[0], w[3]);
+  w[5] = cmul(w[1], w[3]);
+  w[6] = cmul(w[2], w[3]);
+}
+
+// The product H = Nhat M on the packed transforms.  Plane 0 holds
+// Z = M1 + i M2, so M1(k) = (Z(k) + conj Z(-k)) / 2 and
+// M2(k) = (Z(k) - conj Z(-k)) / 2i; plane 1 holds M3.  The result is packed
+// the same way (H1 + i H2, H3).  e: the tensor at k; z, zm: Z at k and -k.
+__device__ inline void demag_apply(const double* e, double2 z, double2 zm, double2 m3, double2& o0, double2& o1) {
+  const double2 m1 = make_double2(0.5 * (z.x + zm.x), 0.5 * (z.y - zm.y));
+  const double2 m2 = make_double2(0.5 * (z.y + zm.y), -0.5 * (z.x - zm.x));
+  const double xx = e[0], yy = e[1], zz = e[2], xy = e[3], xz = e[4], yz = e[5];
+  const double2 h1 = make_double2(xx * m1.x + xy * m2.x + xz * m3.x, xx * m1.y + xy * m2.y + xz * m3.y);
+  const double2 h2 = make_double2(xy * m1.x + yy * m2.x + yz * m3.x, xy * m1.y + yy * m2.y + yz * m3.y);
+  o1 = make_double2(xz * m1.x + yz * m2.x + zz * m3.x, xz * m1.y + yz * m2.y + zz * m3.y);
+  o0 = make_double2(h1.x - h2.y, h1.y + h2.x);
+}
+
+// The shape of a line transform: threads per line, values per thread, lines
+// per workgroup of NT threads.
+template <int BITS, int NT>
+struct FftShape {
+  static constexpr int L = 1 << BITS;
+  static constexpr int T = L >= 8 ? L / 8 : 1;
+  static constexpr int NR = L >= 8 ? 8 : L;
+  static constexpr int C = NT / T;
+  static constexpr int LP = L + (L >> 3);  // padded line in LDS
+  static constexpr int LDS = L >= 16 ? C * LP : 1;
+};
+
+constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c(v >> 1); }
+
+// The transform of M lines in registers: v[m][r] holds entry j + r T of line m
+// before and after.  Every thread of the workgroup calls it; LDS is free
+// again after the next barrier.  The M lines share a pass's twiddle factors.
+template <int BITS, int NT, bool CF, int M, typename V>
+__device__ inline void fft_regs(V& v, double dir, double2* sm, int c, int j) {
+  using S = FftShape<BITS, NT>;
+  constexpr int L = S::L, T = S::T, C = S::C, LP = S::LP;
+  if constexpr (L <= 8) {
+#pragma unroll
+    for (int m = 0; m < M; ++m) dft<L>(v[m], dir);
+  } else {
+    constexpr int R0 = (BITS % 3 == 0) ? 8 : (1 << (BITS % 3));
+    constexpr int NMID = (BITS - (R0 == 8 ? 3 : BITS % 3)) / 3 - 1;  // radix-8 passes between
+    auto lds = [&](int i) -> double2& { return CF ? sm[(i + (i >> 3)) * C + c] : sm[c * LP + i + (i >> 3)]; };
+    // first pass: butterflies u of radix R0 on registers u + r (8 / R0)
+    constexpr int U = 8 / R0;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      if (m > 0) __syncthreads();
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        double2 w[R0];
+#pragma unroll
+        for (int r = 0; r < R0; ++r) w[r] = v[m][u + r * U];
+        dft<R0>(w, dir);
+        const int jj = j + u * T;
+#pragma unroll
+        for (int r = 0; r < R0; ++r) lds(jj * R0 + r) = w[r];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 8; ++r) v[m][r] = lds(j + r * T);
+    }
+    double2 w[7];
+#pragma unroll
+    for (int mid = 0; mid < NMID; ++mid) {
+      const int ns = R0 << (3 * mid), k = j & (ns - 1);
+      twiddles8(w, dir, k, ilog2c(8 * ns));
+      const int d = (j - k) * 8 + k;
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+#pragma unroll
+        for (int r = 1; r < 8; ++r) v[m][r] = cmul(v[m][r], w[r - 1]);
+        dft<8>(v[m], dir);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 8; ++r) lds(d + r * ns) = v[m][r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[m][r] = lds(j + r * T);
+      }
+    }
+    twiddles8(w, dir, j, BITS);  // ns = L / 8 = T, so k = j
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+#pragma unroll
+      for (int r = 1; r < 8; ++r) v[m][r] = cmul(v[m][r], w[r - 1]);
+      dft<8>(v[m], dir);
+    }
+  }
+}
+
+template <int BITS, int NT, bool CF>
+__global__ __launch_bounds__(NT) void k_fft(double2* __restrict__ data, FftPass p) {
+  using S = FftShape<BITS, NT>;
+  constexpr int T = S::T, NR = S::NR, C = S::C;
+  __shared__ double2 sm[S::LDS];
   const int t = threadIdx.x;
   const int c = CF ? t % C : t / T;
   const int j = CF ? t / C : t % T;
   int64_t g = blockIdx.x;
   if (CF && (gridDim.x & 31) == 0) g = (g & ~(int64_t)31) | ((g & 7) << 2) | ((g >> 3) & 3);
   const int64_t gpo = (p.n_inner + C - 1) / C;
-  const int64_t outer = g / gpo;
-  const int64_t inner = (g - outer * gpo) * C + c;
-  const bool live = inner < p.n_inner;
+  const int64_t outer = (uint32_t)g / (uint32_t)gpo, first = (g - outer * gpo) * C;
+  const int64_t n_inner = blockIdx.y == 0 ? p.n_inner : p.n_inner1;
+  if (first >= n_inner) return;
+  const int64_t inner = first + c;
+  const bool live = inner < n_inner;
   double2* line = data + (int64_t)blockIdx.y * p.plane_stride + (live ? inner : 0) * p.inner_stride +
                   outer * p.outer_stride;
   const double dir = (double)p.dir;
-  auto lds = [&](int i) -> double2& { return CF ? sm[(i + (i >> 3)) * C + c] : sm[c * LP + i + (i >> 3)]; };
-  double2 v[NR];
+  double2 v[1][NR];
 #pragma unroll
   for (int q = 0; q < NR; ++q) {
     const int i = j + q * T;
-    v[q] = (live && i < p.n_load) ? line[(int64_t)i * p.s] : make_double2(0.0, 0.0);
+    v[0][q] = (live && i < p.n_load) ? line[(int64_t)i * p.s] : make_double2(0.0, 0.0);
   }
-  if constexpr (L <= 8) {  // one pass
-    dft<NR>(v, dir);
+  fft_regs<BITS, NT, CF, 1>(v, dir, sm, c, j);
 #pragma unroll
-    for (int q = 0; q < NR; ++q)
-      if (live && q < p.n_store) line[(int64_t)q * p.s] = make_double2(v[q].x * p.scale, v[q].y * p.scale);
-    return;
-  } else {
-    // first pass: butterflies u of radix R0 on registers u + r (8 / R0)
-    constexpr int U = 8 / R0;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      double2 w[R0];
-#pragma unroll
-      for (int r = 0; r < R0; ++r) w[r] = v[u + r * U];
-      dft<R0>(w, dir);
-      const int jj = j + u * T;
-#pragma unroll
-      for (int r = 0; r < R0; ++r) lds(jj * R0 + r) = w[r];
+  for (int q = 0; q < NR; ++q) {
+    const int i = j + q * T;
+    if (live && i < p.n_store) line[(int64_t)i * p.s] = make_double2(v[0][q].x * p.scale, v[0][q].y * p.scale);
+  }
+}
+
+// ---------------------------------------------- fused ends of the convolution
+// The x transforms read the field itself (m~1 + i m~2 into plane 0, m~3 into
+// plane 1) and, at the end, write h itself: the padded copy of the field and
+// the copy back take no pass of their own.  m~3 is real, so plane 1 holds the
+// columns kx <= px / 2 only, on the way there and back.  A row's two planes
+// share a workgroup where a line leaves room for it, so that the 24 bytes of
+// a node are read and written from one CU.  Bound by HBM and by the latency
+// of one round of workgroups: 1024^2 23 us each (25 + 14 us for the transform
+// and the padded copy, 25 + 10 at the end), 120 x 90 x 50 15 us (16 + 9, 16 + 7).
+struct FieldRows {
+  int64_t nx, rows, px, py, ny;  // cells of a row, rows of the box, padded lengths
+  int64_t plane;
+};
+template <int C>
+struct RowLine {
+  int64_t row;
+  int plane;
+  bool live;
+  __device__ RowLine(const FieldRows& f, int c) {
+    if (C > 1) {
+      row = (int64_t)blockIdx.x * (C / 2) + c / 2;
+      plane = c & 1;
+    } else {
+      row = blockIdx.x;
+      plane = (int)blockIdx.y;
     }
-    int ns = R0;
+    live = row < f.rows;
+    if (!live) row = 0;
+  }
+  __device__ int64_t line(const FieldRows& f) const {
+    const int64_t b = (uint32_t)row / (uint32_t)f.ny;  // rows < 2^31
+    return plane * f.plane + f.px * (row - b * f.ny + f.py * b);
+  }
+};
+
+template <int BITS, int NT>
+__global__ __launch_bounds__(NT) void k_fft_field_in(FieldRows f, const double* __restrict__ m,
+                                                     const double* __restrict__ mprev, double2* __restrict__ w) {
+  using S = FftShape<BITS, NT>;
+  __shared__ double2 sm[S::LDS];
+  const int c = (int)threadIdx.x / S::T, j = (int)threadIdx.x % S::T;
+  const RowLine<S::C> r(f, c);
+  double2 v[1][S::NR];
 #pragma unroll
-    for (int m = 0; m < NMID; ++m) {
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < 8; ++r) v[r] = lds(j + r * T);
-      __syncthreads();
-      const int k = j % ns;
-      twiddle8(v, dir * 2.0 * (double)k / (double)(8 * ns));
-      dft<8>(v, dir);
-      const int d = (j / ns) * ns * 8 + k;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) lds(d + r * ns) = v[r];
-      ns *= 8;
+  for (int q = 0; q < S::NR; ++q) {
+    const int64_t i = j + q * S::T;
+    v[0][q] = make_double2(0.0, 0.0);
+    if (r.live && i < f.nx) {
+      const int64_t o = 3 * (r.row * f.nx + i) + (r.plane ? 2 : 0);
+      v[0][q].x = mprev ? 2.0 * m[o] - mprev[o] : m[o];
+      if (!r.plane) v[0][q].y = mprev ? 2.0 * m[o + 1] - mprev[o + 1] : m[o + 1];
     }
-    __syncthreads();
+  }
+  fft_regs<BITS, NT, false, 1>(v, -1.0, sm, c, j);
+  if (!r.live) return;
+  double2* line = w + r.line(f);
+  const int last = r.plane ? S::L / 2 : S::L - 1;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) v[r] = lds(j + r * T);
-    twiddle8(v, dir * 2.0 * (double)j / (double)L);  // ns = L / 8 = T, so k = j
-    dft<8>(v, dir);
-    if (live) {
+  for (int q = 0; q < S::NR; ++q) {
+    const int i = j + q * S::T;
+    if (i <= last) line[i] = v[0][q];
+  }
+}
+
+// h = -N * m: plane 0 gives h1 + i h2, plane 1 h3
+template <int BITS, int NT>
+__global__ __launch_bounds__(NT) void k_fft_field_out(FieldRows f, const double2* __restrict__ w, double scale,
+                                                      double* __restrict__ h) {
+  using S = FftShape<BITS, NT>;
+  __shared__ double2 sm[S::LDS];
+  const int c = (int)threadIdx.x / S::T, j = (int)threadIdx.x % S::T;
+  const RowLine<S::C> r(f, c);
+  const double2* line = w + r.line(f);
+  double2 v[1][S::NR];
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int i = j + r * T;
-        if (i < p.n_store) line[(int64_t)i * p.s] = make_double2(v[r].x * p.scale, v[r].y * p.scale);
+  for (int q = 0; q < S::NR; ++q) {
+    const int i = j + q * S::T;
+    const bool conj = r.plane && i > S::L / 2;
+    v[0][q] = r.live ? line[conj ? S::L - i : i] : make_double2(0.0, 0.0);
+    if (conj) v[0][q].y = -v[0][q].y;
+  }
+  fft_regs<BITS, NT, false, 1>(v, 1.0, sm, c, j);
+  if (!r.live) return;
+#pragma unroll
+  for (int q = 0; q < S::NR; ++q) {
+    const int64_t i = j + q * S::T;
+    if (i >= f.nx) continue;
+    const int64_t o = 3 * (r.row * f.nx + i) + (r.plane ? 2 : 0);
+    h[o] = -(v[0][q].x * scale);
+    if (!r.plane) h[o + 1] = -(v[0][q].y * scale);
+  }
+}
+
+// The lines of the last axis, in pairs a = (kx, ky), b = (-kx, -ky): the
+// product at k needs the transform at -k.  Pairs run over kx < px / 2 and all
+// ky.  The columns kx = 0 and kx = px / 2, which mirror into themselves, share
+// the turns of kx = 0: (0, ky) with (0, -ky) for ky < py / 2, (px / 2, ky)
+// with (px / 2, -ky) above; where a line is its own mirror ("self": ky = 0,
+// py / 2) the turn has a = (0, ky) and b = (px / 2, ky).
+struct FusedPass {
+  int64_t px, py;  // lines: kx < px, ky < py (1 where the last axis is y)
+  int64_t s;       // stride of the last axis
+  int64_t plane;   // values of a plane
+  int n;           // cells along the last axis
+  int hb;          // px / 2 = 2^hb
+};
+struct LinePair {
+  int64_t ax, ky, bx, my;
+  bool live, self;
+  __device__ LinePair(const FusedPass& p, int64_t at) {
+    const int64_t half = (int64_t)1 << p.hb;
+    live = at < half * p.py;
+    ky = live ? at >> p.hb : 0;
+    my = (p.py - ky) & (p.py - 1);
+    ax = at & (half - 1);
+    bx = (p.px - ax) & (p.px - 1);
+    self = live && ax == 0 && ky == my;
+    if (self) bx = half;
+    if (ax == 0 && ky > my) ax = bx = half;
+  }
+};
+
+// The tensor's transform at entry k of line (kx, ky), kx <= px / 2.  It is
+// real, even or odd along each axis, and only its octant is read: xy is odd
+// along y, xz along z, yz along both; in 2D (FLAT) the last axis is y and xz
+// and yz are zero.
+template <bool FLAT>
+__device__ inline void demag_entry(const FusedPass& p, const double* __restrict__ nhat, int64_t kx, int64_t ky,
+                                   int k, int L, double* e) {
+  const int64_t my = (p.py - ky) & (p.py - 1);
+  const bool far = k > L / 2;
+  const double* t = nhat + kx + p.px * (ky <= my ? ky : my) + (int64_t)(far ? L - k : k) * p.s;
+  const double sy = ky <= my ? 1.0 : -1.0, sl = far ? -1.0 : 1.0;
+  e[0] = t[0];
+  e[1] = t[p.plane];
+  e[2] = t[2 * p.plane];
+  e[3] = t[3 * p.plane] * (FLAT ? sl : sy);
+  e[4] = FLAT ? 0.0 : t[4 * p.plane] * sl;
+  e[5] = FLAT ? 0.0 : t[5 * p.plane] * (sy * sl);
+}
+
+// The last axis in one kernel: forward transform, product with the tensor and
+// inverse transform of a pair of lines without leaving the registers.  b is
+// read backwards, so that a thread holds k of the one and -k of the other.
+// Plane 1 is real in space: its line b is the conjugate of its line a and is
+// neither read nor transformed.  Self lines are read forwards and their
+// values at -k come through LDS; plane 1 is real along them, so its two lines
+// are packed as a + i b.
+// Bound by the requests of the strided loads (a wavefront's load takes a clock
+// for each 128-byte line that it touches, C lines of 16 bytes abreast), then
+// by latency at two wavefronts per SIMD: the three arrays take 96 registers
+// of a thread.  120 x 90 x 50 (128 entries): 77 us, against 304 us for a
+// pass each way and the product on all of the tensor between; 1024^2: 92 us
+// against 198 us.  Workgroups of 128 threads where a line leaves the choice
+// (120 x 90 x 50: 80 us with 256, 103 with 512), of 512 for 2048 entries and
+// more (1024^2: 118 us with 256, which leaves one line abreast).
+template <int BITS, int NT, bool FLAT>
+__global__ __launch_bounds__(NT, 2) void k_fft_demag(double2* __restrict__ w, const double* __restrict__ nhat,
+                                                  FusedPass p) {
+  using S = FftShape<BITS, NT>;
+  constexpr int L = S::L, T = S::T, C = S::C, NR = S::NR;
+  __shared__ double2 sm[S::LDS];
+  const int c = (int)threadIdx.x % C;
+  int j = (int)threadIdx.x / C;
+  int64_t g = blockIdx.x;
+  if ((gridDim.x & 31) == 0) g = (g & ~(int64_t)31) | ((g & 7) << 2) | ((g >> 3) & 3);
+  const LinePair l(p, g * C + c);
+  const bool live = l.live, self = l.self;
+  const int n = p.n;
+  double2* la = w + l.ax + p.px * l.ky;
+  double2* lb = w + l.bx + p.px * l.my;
+  double2 v[3][NR];  // planes 0 and 1 of line a, plane 0 of line b
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const double2 zero = make_double2(0.0, 0.0);
+    const int i = j + q * T, r = self ? i : (L - i) & (L - 1);
+    v[0][q] = live && i < n ? la[(int64_t)i * p.s] : zero;
+    v[1][q] = live && i < n ? la[p.plane + (int64_t)i * p.s] : zero;
+    v[2][q] = live && r < n ? lb[(int64_t)r * p.s] : zero;
+    if (self && i < n) v[1][q].y = lb[p.plane + (int64_t)i * p.s].x;
+  }
+  // no addresses or twiddle factors kept across the transforms, for the registers
+  asm volatile("" : "+v"(j));
+  fft_regs<BITS, NT, true, 3>(v, -1.0, sm, c, j);
+  __syncthreads();
+  // the turns 0 and py / 2 of kx = 0 (the same on the whole workgroup)
+  const int64_t mid = p.py > 1 ? p.py / 2 << p.hb : 0;
+  const bool any_self = g == 0 || g == mid / C;
+  double2 m3b[NR];
+  if (any_self) {
+    auto mirrored = [&](const double2* x, double2* o) {  // x at -k
+      if constexpr (T == 1) {
+#pragma unroll
+        for (int q = 0; q < NR; ++q) o[q] = x[(L - q) & (L - 1)];
+      } else {
+        auto lds = [&](int i) -> double2& { return sm[(i + (i >> 3)) * C + c]; };
+#pragma unroll
+        for (int q = 0; q < NR; ++q) lds(j + q * T) = x[q];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NR; ++q) o[q] = lds((L - (j + q * T)) & (L - 1));
+        __syncthreads();
+      }
+    };
+    double2 o[NR];
+    double e[6];
+    mirrored(v[1], o);
+    if (self) {
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        const double2 z = v[1][q], zm = o[q];
+        v[1][q] = make_double2(0.5 * (z.x + zm.x), 0.5 * (z.y - zm.y));
+        m3b[q] = make_double2(0.5 * (z.y + zm.y), -0.5 * (z.x - zm.x));
+      }
+    }
+    mirrored(v[0], o);
+    if (self) {
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        demag_entry<FLAT>(p, nhat, l.ax, l.ky, j + q * T, L, e);
+        demag_apply(e, v[0][q], o[q], v[1][q], v[0][q], v[1][q]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    mirrored(v[2], o);
+    if (self) {
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        double2 h3;
+        demag_entry<FLAT>(p, nhat, l.bx, l.ky, j + q * T, L, e);
+        demag_apply(e, v[2][q], o[q], m3b[q], v[2][q], h3);
+        v[1][q] = make_double2(v[1][q].x - h3.y, v[1][q].y + h3.x);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
+  if (!self) {
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const double2 za = v[0][q], zb = v[2][q], m3 = v[1][q];
+      double e[6];
+      double2 none;
+      demag_entry<FLAT>(p, nhat, l.ax, l.ky, j + q * T, L, e);
+      demag_apply(e, za, zb, m3, v[0][q], v[1][q]);
+      demag_apply(e, zb, za, make_double2(m3.x, -m3.y), v[2][q], none);
+      if (q & 1) __builtin_amdgcn_sched_barrier(0);  // two entries' loads at a time
+    }
+  }
+  asm volatile("" : "+v"(j));
+  fft_regs<BITS, NT, true, 3>(v, 1.0, sm, c, j);
+  asm volatile("" : "+v"(j));
+  if (!live) return;
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const int i = j + q * T, r = self ? i : (L - i) & (L - 1);
+    if (r < n) lb[(int64_t)r * p.s] = v[2][q];
+    if (i >= n) continue;
+    la[(int64_t)i * p.s] = v[0][q];
+    la[p.plane + (int64_t)i * p.s] = self ? make_double2(v[1][q].x, 0.0) : v[1][q];
+    if (self) lb[p.plane + (int64_t)i * p.s] = make_double2(v[1][q].y, 0.0);
+    if (!self && l.ax == l.bx) lb[p.plane + (int64_t)i * p.s] = make_double2(v[1][q].x, -v[1][q].y);
+  }
+}
+
+// The same with a pair's three arrays (planes 0 and 1 of line a, plane 0 of
+// line b) in the hands of S threads each, for grids that leave most of the
+// chip idle: a third of the chain of transforms (200^2: 13 us against 18),
+// but three times the twiddle factors and reads of the tensor (120 x 90 x 50:
+// 113 us against 77).  The product reads the other arrays through LDS.
+template <int BITS, int S, bool FLAT>
+__global__ __launch_bounds__(3 * S, 3) void k_fft_demag3(double2* __restrict__ w, const double* __restrict__ nhat,
+                                                         FusedPass p) {
+  using F = FftShape<BITS, S>;
+  constexpr int L = F::L, T = F::T, C = F::C, NR = F::NR, ARR = C * F::LP;
+  __shared__ double2 sm[3 * ARR];
+  const int grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / S), tid = (int)threadIdx.x % S;
+  const int c = tid % C;
+  int j = tid / C;
+  int64_t g = blockIdx.x;
+  if ((gridDim.x & 31) == 0) g = (g & ~(int64_t)31) | ((g & 7) << 2) | ((g >> 3) & 3);
+  const LinePair l(p, g * C + c);
+  const bool live = l.live, self = l.self;
+  const int n = p.n;
+  double2* la = w + l.ax + p.px * l.ky;
+  double2* lb = w + l.bx + p.px * l.my;
+  double2* line = grp == 0 ? la : grp == 1 ? la + p.plane : lb;
+  const bool back = grp == 2 && !self;  // line b is read backwards
+  double2 v[1][NR];
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const int i = j + q * T, r = back ? (L - i) & (L - 1) : i;
+    v[0][q] = live && r < n ? line[(int64_t)r * p.s] : make_double2(0.0, 0.0);
+    if (grp == 1 && self && r < n) v[0][q].y = lb[p.plane + (int64_t)r * p.s].x;
+  }
+  asm volatile("" : "+v"(j));  // addresses and twiddle factors are not kept across the transforms
+  double2* own = sm + grp * ARR;
+  fft_regs<BITS, S, true, 1>(v, -1.0, own, c, j);
+  __syncthreads();
+  auto idx = [&](int i) { return (i + (i >> 3)) * C + c; };
+#pragma unroll
+  for (int q = 0; q < NR; ++q) own[idx(j + q * T)] = v[0][q];
+  __syncthreads();
+  const int64_t nx = self ? l.bx : l.ax;  // line b's column of the tensor
+  const double2 *a0 = sm, *a1 = sm + ARR, *b0 = sm + 2 * ARR;
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const int k = j + q * T, ik = idx(k), im = idx((L - k) & (L - 1));
+    double e[6];
+    double2 none, m3 = a1[ik], m3b = make_double2(m3.x, -m3.y);
+    if (self) {
+      const double2 z = m3, zm = a1[im];
+      m3 = make_double2(0.5 * (z.x + zm.x), 0.5 * (z.y - zm.y));
+      m3b = make_double2(0.5 * (z.y + zm.y), -0.5 * (z.x - zm.x));
+    }
+    if (grp == 0) {
+      demag_entry<FLAT>(p, nhat, l.ax, l.ky, k, L, e);
+      demag_apply(e, v[0][q], self ? a0[im] : b0[ik], m3, v[0][q], none);
+    } else if (grp == 1) {
+      demag_entry<FLAT>(p, nhat, l.ax, l.ky, k, L, e);
+      demag_apply(e, a0[ik], self ? a0[im] : b0[ik], m3, none, v[0][q]);
+      if (self) {
+        double2 h;
+        demag_entry<FLAT>(p, nhat, nx, l.ky, k, L, e);
+        demag_apply(e, b0[ik], b0[im], m3b, none, h);
+        v[0][q] = make_double2(v[0][q].x - h.y, v[0][q].y + h.x);
+      }
+    } else {
+      demag_entry<FLAT>(p, nhat, nx, l.ky, k, L, e);
+      demag_apply(e, v[0][q], self ? b0[im] : a0[ik], m3b, v[0][q], none);
+    }
+  }
+  __syncthreads();
+  asm volatile("" : "+v"(j));
+  fft_regs<BITS, S, true, 1>(v, 1.0, own, c, j);
+  asm volatile("" : "+v"(j));
+  if (!live) return;
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const int i = j + q * T, r = back ? (L - i) & (L - 1) : i;
+    if (r >= n) continue;
+    line[(int64_t)r * p.s] = grp == 1 && self ? make_double2(v[0][q].x, 0.0) : v[0][q];
+    if (grp == 1 && self) lb[p.plane + (int64_t)r * p.s] = make_double2(v[0][q].y, 0.0);
+    if (grp == 1 && !self && l.ax == l.bx) lb[p.plane + (int64_t)r * p.s] = make_double2(v[0][q].x, -v[0][q].y);
+  }
+}
+
+// The product by itself, for long lines that are too few to fill the chip:
+// there the transforms run plane by plane and line by line in passes of their
+// own (5 x 2048: 52 us for the last axis in one kernel).
+template <bool FLAT>
+__global__ void k_demag_pairs(double2* __restrict__ w, const double* __restrict__ nhat, FusedPass p, int L) {
+  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, lines = p.py << p.hb;
+  if (x >= lines * L) return;
+  const int k = (int)(x / lines), m = (L - k) & (L - 1);
+  const LinePair l(p, x % lines);
+  if (l.self && k > m) return;  // done with -k
+  for (int u = 0; u < (l.self ? 2 : 1); ++u) {
+    const int64_t ax = u ? l.bx : l.ax, bx = l.self ? ax : l.bx;
+    double2* a = w + ax + p.px * l.ky + k * p.s;
+    double2* b = w + bx + p.px * l.my + m * p.s;
+    const double2 z = a[0], zm = b[0], m3 = a[p.plane];
+    double e[6];
+    double2 o0, o1, r0, r1;
+    demag_entry<FLAT>(p, nhat, ax, l.ky, k, L, e);
+    demag_apply(e, z, zm, m3, o0, o1);
+    demag_apply(e, zm, z, make_double2(m3.x, -m3.y), r0, r1);
+    a[0] = o0;
+    a[p.plane] = o1;
+    if (a == b) continue;
+    b[0] = r0;
+    if (ax == bx) b[p.plane] = r1;
+  }
+}
+
+// Workgroups of 512 threads; of 128 where the larger leave CUs without one
+// (and a line fits): 200^2, 50 workgroups of an x pass, 6.5 -> 4.9 us.
+constexpr int64_t FFT_FEW = 256;
+// Workgroups of the kernel with an array per S threads up to which it is
+// taken: four to a CU run at once (100 x 100 x 4: 10 us against 12; 50 x 60 x
+// 33, 4096 of them: 32 us against 26).
+constexpr int64_t DEMAG_FEW = 1024;
+template <int BITS>
+constexpr bool fft_narrow() {
+  return FftShape<BITS, 512>::T <= 128;
 }
 
 template <int BITS, bool CF>
 void launch_fft_t(hipStream_t st, double2* data, const FftPass& p, int64_t n_outer, int planes) {
-  constexpr int L = 1 << BITS;
-  constexpr int T = L >= 8 ? L / 8 : 1;
-  constexpr int C = 512 / T;
-  const int64_t groups = ((p.n_inner + C - 1) / C) * n_outer;
-  hipLaunchKernelGGL((k_fft<BITS, CF>), dim3((unsigned)groups, (unsigned)planes), dim3(512), 0, st, data, p);
+  auto go = [&](auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    const int64_t groups = ceil_div(p.n_inner, FftShape<BITS, NT>::C) * n_outer;
+    if (NT > 128 && fft_narrow<BITS>() && groups * planes < FFT_FEW) return false;
+    hipLaunchKernelGGL((k_fft<BITS, NT, CF>), dim3((unsigned)groups, (unsigned)planes), dim3(NT), 0, st, data, p);
+    return true;
+  };
+  if (go(std::integral_constant<int, 512>{})) return;
+  if constexpr (fft_narrow<BITS>()) go(std::integral_constant<int, 128>{});
 }
 
 template <bool CF>
@@ -389,15 +838,16 @@ int ilog2(int64_t v) {
   return b;
 }
 
-// One transform along one axis, lines (inner, outer) of `planes` planes of P
+// One transform along one axis, lines (inner, outer; of plane 1 only inner < n_inner1) of `planes` planes of P
 // values: elements i < n_load are read (the rest taken as zero), i < n_store
 // written; the inverse pass that ends a transform is scaled by 1 / P.
 void fft_axis(hipStream_t st, double2* data, int64_t P, int planes, int64_t L, int64_t s, int64_t n_inner,
-              int64_t inner_stride, int64_t n_outer, int64_t outer_stride, int64_t n_load, int64_t n_store, int dir,
+              int64_t n_inner1, int64_t inner_stride, int64_t n_outer, int64_t outer_stride, int64_t n_load, int64_t n_store, int dir,
               double scale) {
   if (L <= 1) return;
   FftPass p;
   p.n_inner = n_inner;
+  p.n_inner1 = n_inner1;
   p.inner_stride = inner_stride;
   p.outer_stride = outer_stride;
   p.s = s;
@@ -412,32 +862,12 @@ void fft_axis(hipStream_t st, double2* data, int64_t P, int planes, int64_t L, i
     launch_fft_cf<true>(st, ilog2(L), data, p, n_outer, planes);
 }
 
-// Forward transform of `planes` planes holding values on the n-box only (the
-// rest of the padded grid is never read: zero by construction), every axis
-// pruned to the lines that can hold nonzero values.
-void fft_forward_box(hipStream_t st, FieldDims f, double2* w, int planes) {
-  const int64_t P = f.px * f.py * f.pz, pxy = f.px * f.py;
-  fft_axis(st, w, P, planes, f.px, 1, f.ny, f.px, f.nz, pxy, f.nx, f.px, -1, 1.0);
-  fft_axis(st, w, P, planes, f.py, f.px, f.px, 1, f.nz, pxy, f.ny, f.py, -1, 1.0);
-  fft_axis(st, w, P, planes, f.pz, pxy, pxy, 1, 1, 0, f.nz, f.pz, -1, 1.0);
-}
-
-// Inverse transform, scaled by 1 / P, of which only the n-box is written.
-void fft_inverse_box(hipStream_t st, FieldDims f, double2* w, int planes) {
-  const int64_t P = f.px * f.py * f.pz, pxy = f.px * f.py;
-  const double sc = 1.0 / (double)P;
-  const bool z = f.pz > 1;
-  if (z) fft_axis(st, w, P, planes, f.pz, pxy, pxy, 1, 1, 0, f.pz, f.nz, +1, 1.0);
-  fft_axis(st, w, P, planes, f.py, f.px, f.px, 1, f.nz, pxy, f.py, f.ny, +1, 1.0);
-  fft_axis(st, w, P, planes, f.px, 1, f.ny, f.px, f.nz, pxy, f.px, f.nx, +1, sc);
-}
-
 // Forward transform of `planes` full padded planes.
 void fft_forward_full(hipStream_t st, FieldDims f, double2* w, int planes) {
   const int64_t P = f.px * f.py * f.pz, pxy = f.px * f.py;
-  fft_axis(st, w, P, planes, f.px, 1, f.py, f.px, f.pz, pxy, f.px, f.px, -1, 1.0);
-  fft_axis(st, w, P, planes, f.py, f.px, f.px, 1, f.pz, pxy, f.py, f.py, -1, 1.0);
-  fft_axis(st, w, P, planes, f.pz, pxy, pxy, 1, 1, 0, f.pz, f.pz, -1, 1.0);
+  fft_axis(st, w, P, planes, f.px, 1, f.py, f.py, f.px, f.pz, pxy, f.px, f.px, -1, 1.0);
+  fft_axis(st, w, P, planes, f.py, f.px, f.px, f.px, 1, f.pz, pxy, f.py, f.py, -1, 1.0);
+  fft_axis(st, w, P, planes, f.pz, pxy, pxy, pxy, 1, 1, 0, f.pz, f.pz, -1, 1.0);
 }
 
 // Two tensor components packed as one complex plane, a + i b, on the padded
@@ -477,89 +907,17 @@ __global__ void k_take_pair(int64_t P, int c0, int c1, const double2* in, double
 }
 
 // ------------------------------------------------------------ field terms
-// m~ (m^n, or 2 m^n - m^{n-1}) into two padded planes: m~1 + i m~2 and m~3,
-// on the n-box only
-__global__ void k_pad_field(FieldDims f, const double* m, const double* mprev, double2* out) {
-  const int64_t node = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t N = f.nx * f.ny * f.nz;
-  if (node >= N) return;
-  const int64_t P = f.px * f.py * f.pz;
-  const int64_t a = node % f.nx, b = (node / f.nx) % f.ny, c = node / (f.nx * f.ny);
-  const int64_t p = a + f.px * (b + f.py * c);
-  double x[3];
-  for (int k = 0; k < 3; ++k) x[k] = mprev ? 2.0 * m[3 * node + k] - mprev[3 * node + k] : m[3 * node + k];
-  out[p] = make_double2(x[0], x[1]);
-  out[P + p] = make_double2(x[2], 0.0);
-}
-
-// The product H = Nhat M on the packed transforms.  Plane 0 holds
-// Z = M1 + i M2, so M1(k) = (Z(k) + conj Z(-k)) / 2 and
-// M2(k) = (Z(k) - conj Z(-k)) / 2i; plane 1 holds M3.  The result is packed
-// the same way (H1 + i H2, H3); each thread does the pair k, -k.
-__device__ inline void demag_apply(const double* nhat, int64_t P, int64_t p, double2 z, double2 zm, double2 m3,
-                                   double2& o0, double2& o1) {
-  const double2 m1 = make_double2(0.5 * (z.x + zm.x), 0.5 * (z.y - zm.y));
-  const double2 m2 = make_double2(0.5 * (z.y + zm.y), -0.5 * (z.x - zm.x));
-  const double xx = nhat[p], yy = nhat[P + p], zz = nhat[2 * P + p];
-  const double xy = nhat[3 * P + p], xz = nhat[4 * P + p], yz = nhat[5 * P + p];
-  const double2 h1 = make_double2(xx * m1.x + xy * m2.x + xz * m3.x, xx * m1.y + xy * m2.y + xz * m3.y);
-  const double2 h2 = make_double2(xy * m1.x + yy * m2.x + yz * m3.x, xy * m1.y + yy * m2.y + yz * m3.y);
-  o1 = make_double2(xz * m1.x + yz * m2.x + zz * m3.x, xz * m1.y + yz * m2.y + zz * m3.y);
-  o0 = make_double2(h1.x - h2.y, h1.y + h2.x);
-}
-
-__global__ void k_demag_mul(FieldDims f, const double* nhat, double2* w) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t P = f.px * f.py * f.pz;
-  if (p >= P) return;
-  const int64_t a = p % f.px, b = (p / f.px) % f.py, c = p / (f.px * f.py);
-  const int64_t q = ((f.px - a) & (f.px - 1)) + f.px * (((f.py - b) & (f.py - 1)) + f.py * ((f.pz - c) & (f.pz - 1)));
-  if (q < p) return;  // done by the partner
-  const double2 zp = w[p], zq = w[q], m3p = w[P + p], m3q = w[P + q];
-  double2 o0, o1;
-  demag_apply(nhat, P, p, zp, zq, m3p, o0, o1);
-  if (q != p) {
-    double2 r0, r1;
-    demag_apply(nhat, P, q, zq, zp, m3q, r0, r1);
-    w[q] = r0;
-    w[P + q] = r1;
-  }
-  w[p] = o0;
-  w[P + p] = o1;
-}
-
-// h = -N * m from the inverse transform: plane 0 = h1 + i h2, plane 1 = h3
-__global__ void k_stray_out(FieldDims f, const double2* w, double* h) {
-  const int64_t node = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t N = f.nx * f.ny * f.nz;
-  if (node >= N) return;
-  const int64_t P = f.px * f.py * f.pz;
-  const int64_t a = node % f.nx, b = (node / f.nx) % f.ny, c = node / (f.nx * f.ny);
-  const int64_t p = a + f.px * (b + f.py * c);
-  const double2 v = w[p];
-  h[3 * node] = -v.x;
-  h[3 * node + 1] = -v.y;
-  h[3 * node + 2] = -w[P + p].x;
-}
-
 // b -= dt' (m~ x f + alpha m~ x (m~ x f)), f = (h_s + h_e) - q (0, m~2, m~3);
 // prm: [0] alpha, [2] dt', [3] q, [4..6] h_e
-__global__ void k_field_rhs(int64_t N, const double* prm, const double* m, const double* mprev, FieldDims f,
-                            const double2* w, double* b) {
+__global__ void k_field_rhs(int64_t N, const double* prm, const double* m, const double* mprev, const double* h,
+                            double* b) {
   const int64_t node = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (node >= N) return;
   const double alpha = prm[0], dtp = prm[2], q = prm[3];
   double x[3], hs[3] = {0.0, 0.0, 0.0};
   for (int k = 0; k < 3; ++k) x[k] = mprev ? 2.0 * m[3 * node + k] - mprev[3 * node + k] : m[3 * node + k];
-  if (w) {
-    const int64_t P = f.px * f.py * f.pz;
-    const int64_t a = node % f.nx, bb = (node / f.nx) % f.ny, c = node / (f.nx * f.ny);
-    const int64_t p = a + f.px * (bb + f.py * c);
-    const double2 v = w[p];
-    hs[0] = -v.x;
-    hs[1] = -v.y;
-    hs[2] = -w[P + p].x;
-  }
+  if (h)
+    for (int k = 0; k < 3; ++k) hs[k] = h[3 * node + k];
   const double fp[3] = {hs[0] + prm[4], (hs[1] + prm[5]) - q * x[1], (hs[2] + prm[6]) - q * x[2]};
   const double c1[3] = {x[1] * fp[2] - x[2] * fp[1], x[2] * fp[0] - x[0] * fp[2], x[0] * fp[1] - x[1] * fp[0]};
   const double c2[3] = {x[1] * c1[2] - x[2] * c1[1], x[2] * c1[0] - x[0] * c1[2], x[0] * c1[1] - x[1] * c1[0]};
@@ -642,6 +1000,7 @@ void launch_demag_pair(hipStream_t st, FieldDims f, int c0, int c1, const double
 void launch_demag_setup(hipStream_t st, FieldDims f, double2* work, double* nhat) {
   const int64_t P = f.px * f.py * f.pz;
   double* T = (double*)(work + P);
+  hipLaunchKernelGGL(k_fft_unit, dim3((1 << FFT_MAX_BITS) / TPB), dim3(TPB), 0, st);
   launch_demag_table(st, f, T);
   const int pairs[3][2] = {{0, 1}, {2, 3}, {4, 5}};
   for (int r = 0; r < 3; ++r) {
@@ -692,8 +1051,7 @@ hipError_t stray_noalloc(FieldDims f, const double* m, double* h, hipStream_t st
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  launch_stray(st, f, m, nullptr, nhat, work);
-  launch_stray_out(st, f, work, h);
+  launch_stray(st, f, m, nullptr, nhat, work, h);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = hipStreamSynchronize(st);
@@ -704,23 +1062,89 @@ hipError_t stray_noalloc(FieldDims f, const double* m, double* h, hipStream_t st
   return hipSuccess;
 }
 
-void launch_stray(hipStream_t st, FieldDims f, const double* m, const double* mprev, const double* nhat,
-                  double2* work) {
-  const int64_t P = f.px * f.py * f.pz, N = f.nx * f.ny * f.nz;
-  hipLaunchKernelGGL(k_pad_field, dim3(nblk(N)), dim3(TPB), 0, st, f, m, mprev, work);
-  fft_forward_box(st, f, work, 2);
-  hipLaunchKernelGGL(k_demag_mul, dim3(nblk(P)), dim3(TPB), 0, st, f, nhat, work);
-  fft_inverse_box(st, f, work, 2);
+namespace {
+template <int BITS>
+void launch_field_rows(hipStream_t st, const FieldRows& f, const double* m, const double* mprev, double2* w,
+                       double scale, double* h) {
+  auto go = [&](auto nt) {
+    constexpr int NT = decltype(nt)::value, C = FftShape<BITS, NT>::C;
+    const dim3 g((unsigned)(C > 1 ? ceil_div(f.rows, C / 2) : f.rows), C > 1 ? 1 : 2);
+    if (NT > 128 && fft_narrow<BITS>() && g.x * g.y < FFT_FEW) return false;
+    if (h)
+      hipLaunchKernelGGL((k_fft_field_out<BITS, NT>), g, dim3(NT), 0, st, f, w, scale, h);
+    else
+      hipLaunchKernelGGL((k_fft_field_in<BITS, NT>), g, dim3(NT), 0, st, f, m, mprev, w);
+    return true;
+  };
+  if (go(std::integral_constant<int, 512>{})) return;
+  if constexpr (fft_narrow<BITS>()) go(std::integral_constant<int, 128>{});
+}
+template <int BITS, bool FLAT>
+void launch_fft_demag(hipStream_t st, const FusedPass& p, double2* w, const double* nhat) {
+  constexpr int L = 1 << BITS, T = FftShape<BITS, 512>::T, NT = T <= 128 ? 128 : 512;
+  const int64_t lines = p.px / 2 * p.py, groups = ceil_div(lines, FftShape<BITS, NT>::C);
+  if constexpr (T <= 64) {
+    const int64_t few = ceil_div(lines, FftShape<BITS, 64>::C);
+    if (few < DEMAG_FEW) {
+      hipLaunchKernelGGL((k_fft_demag3<BITS, 64, FLAT>), dim3((unsigned)few), dim3(192), 0, st, w, nhat, p);
+      return;
+    }
+  }
+  if (T > 128 && groups < FFT_FEW) {
+    const int64_t all = p.px * p.py, real = FLAT ? p.px / 2 + 1 : all;
+    fft_axis(st, w, p.plane, 2, L, p.s, all, real, 1, 1, 0, p.n, L, -1, 1.0);
+    hipLaunchKernelGGL((k_demag_pairs<FLAT>), dim3(nblk(lines * L)), dim3(TPB), 0, st, w, nhat, p, L);
+    fft_axis(st, w, p.plane, 2, L, p.s, all, real, 1, 1, 0, L, p.n, +1, 1.0);
+    return;
+  }
+  hipLaunchKernelGGL((k_fft_demag<BITS, NT, FLAT>), dim3((unsigned)groups), dim3(NT), 0, st, w, nhat, p);
 }
 
-void launch_stray_out(hipStream_t st, FieldDims f, const double2* work, double* h) {
-  const int64_t N = f.nx * f.ny * f.nz;
-  hipLaunchKernelGGL(k_stray_out, dim3(nblk(N)), dim3(TPB), 0, st, f, work, h);
+// f(integral_constant<ilog2 L>): every axis of a padded grid has 4 cells or more
+template <typename F>
+void for_bits(int64_t L, F f) {
+  switch (ilog2(L)) {
+#define X(B) \
+  case B: return f(std::integral_constant<int, B>{});
+    X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12)
+#undef X
+    default: throw LLG_ERR_UNSUPPORTED;  // lengths are checked when the context is created
+  }
+}
+}  // namespace
+
+// h = -N * m~ (m, or 2 m - mprev), [N][3]: the transforms along x read the
+// field and write h, the last axis is taken there and back in one kernel, and
+// in 3D the y passes stand between.
+void launch_stray(hipStream_t st, FieldDims f, const double* m, const double* mprev, const double* nhat,
+                  double2* work, double* h) {
+  const int64_t P = f.px * f.py * f.pz, pxy = f.px * f.py;
+  const bool flat = f.pz == 1;
+  const FieldRows rows{f.nx, f.ny * f.nz, f.px, f.py, f.ny, P};
+  const FusedPass fused{f.px, flat ? 1 : f.py, flat ? f.px : pxy, P, (int)(flat ? f.ny : f.nz), ilog2(f.px) - 1};
+  auto x_pass = [&](double* out) {
+    for_bits(f.px, [&](auto b) { launch_field_rows<b.value>(st, rows, m, mprev, work, 1.0 / (double)P, out); });
+  };
+  x_pass(nullptr);
+  if (!flat) fft_axis(st, work, P, 2, f.py, f.px, f.px, f.px / 2 + 1, 1, f.nz, pxy, f.ny, f.py, -1, 1.0);
+  if (flat)
+    for_bits(f.py, [&](auto b) { launch_fft_demag<b.value, true>(st, fused, work, nhat); });
+  else
+    for_bits(f.pz, [&](auto b) { launch_fft_demag<b.value, false>(st, fused, work, nhat); });
+  if (!flat) fft_axis(st, work, P, 2, f.py, f.px, f.px, f.px / 2 + 1, 1, f.nz, pxy, f.py, f.ny, +1, 1.0);
+  x_pass(h);
+}
+
+// Room for h in the work planes: past the box in the second plane, which
+// the last x pass does not read (half a plane and more, 8 P >= 32 N bytes).
+double* stray_room(FieldDims f, double2* work) {
+  const int64_t P = f.px * f.py * f.pz;
+  return (double*)(work + P + (f.pz > 1 ? f.px * f.py * f.nz : f.px * f.ny));
 }
 
 void launch_field_rhs(hipStream_t st, int64_t N, const double* prm, const double* m, const double* mprev,
-                      FieldDims f, const double2* work, double* b) {
-  hipLaunchKernelGGL(k_field_rhs, dim3(nblk(N)), dim3(TPB), 0, st, N, prm, m, mprev, f, work, b);
+                      const double* h, double* b) {
+  hipLaunchKernelGGL(k_field_rhs, dim3(nblk(N)), dim3(TPB), 0, st, N, prm, m, mprev, h, b);
 }
 
 }  // namespace llg

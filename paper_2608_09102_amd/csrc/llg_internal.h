@@ -566,17 +566,18 @@ void launch_demag_setup(hipStream_t st, FieldDims f, double2* work, double* nhat
 // c0 + i c1 on the padded grid (cyclic offsets) from it
 void launch_demag_table(hipStream_t st, FieldDims f, double* T);
 void launch_demag_pair(hipStream_t st, FieldDims f, int c0, int c1, const double* T, double2* out);
-// work = the transformed-back product N^ M^ of m~ (m, or 2 m - mprev)
+// h = -N * m~ (m, or 2 m - mprev), [N][3]; work: two planes.  stray_room: where
+// h fits inside work
 void launch_stray(hipStream_t st, FieldDims f, const double* m, const double* mprev, const double* nhat,
-                  double2* work);
-void launch_stray_out(hipStream_t st, FieldDims f, const double2* work, double* h);
+                  double2* work, double* h);
+double* stray_room(FieldDims f, double2* work);
 // the stray field of a device field in the static device array (see
 // llg_stray_field_noalloc); bytes it needs for a padded grid
 size_t stray_noalloc_bytes(FieldDims f);
 hipError_t stray_noalloc(FieldDims f, const double* m, double* h, hipStream_t st);
-// b -= dt' (m~ x f + alpha m~ x (m~ x f)); work NULL: no stray field
+// b -= dt' (m~ x f + alpha m~ x (m~ x f)); h NULL: no stray field
 void launch_field_rhs(hipStream_t st, int64_t N, const double* prm, const double* m, const double* mprev,
-                      FieldDims f, const double2* work, double* b);
+                      const double* h, double* b);
 
 // outer Krylov kernels (FP64)
 template <typename TZ>
