@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "llg_internal.h"
 #include "team.h"
@@ -2578,8 +2579,8 @@ __global__ void k_dense_scatter(int64_t n, const int32_t* __restrict__ sl, const
 
 // In-place Gauss-Jordan inversion with partial pivoting (first largest
 // magnitude in the pivot column), one workgroup.  Row interchanges are undone
-// at the end by swapping columns in reverse order.  The matrix lives in LDS
-// when it fits (a != dense), else in global memory.
+// at the end by swapping columns in reverse order.  The matrix is in global
+// memory.
 constexpr int GJ_T = 1024;
 
 __device__ void gauss_jordan(int64_t nd, double* a, int32_t* piv, int32_t* flag, double* colk,
@@ -2654,98 +2655,157 @@ __device__ void gauss_jordan(int64_t nd, double* a, int32_t* piv, int32_t* flag,
   }
 }
 
-constexpr int64_t GJ_LDS_MAX = 136;  // 136^2 doubles + work arrays fit in 160 KB LDS
+// Largest of v over the wavefront (no NaN), on every lane.
+__device__ inline double wave_max(double v) {
+  auto step = [&](auto ctrl) {
+    constexpr int C = decltype(ctrl)::value;
+    uint64_t u;
+    __builtin_memcpy(&u, &v, 8);
+    // a lane without a source keeps its own value
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)u, (int)(uint32_t)u, C, 0xf, 0xf, false);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_update_dpp((int)(u >> 32), (int)(u >> 32), C, 0xf, 0xf, false);
+    u = (uint64_t)hi << 32 | lo;
+    double o;
+    __builtin_memcpy(&o, &u, 8);
+    v = o > v ? o : v;
+  };
+  step(std::integral_constant<int, 0x111>{});  // row_shr 1, 2, 4, 8
+  step(std::integral_constant<int, 0x112>{});
+  step(std::integral_constant<int, 0x114>{});
+  step(std::integral_constant<int, 0x118>{});
+  step(std::integral_constant<int, 0x142>{});  // row_bcast 15, 31
+  step(std::integral_constant<int, 0x143>{});
+  uint64_t u;
+  __builtin_memcpy(&u, &v, 8);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 63);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(u >> 32), 63);
+  u = (uint64_t)hi << 32 | lo;
+  __builtin_memcpy(&v, &u, 8);
+  return v;
+}
 
-// The same inversion with the matrix in LDS, in three barriers per pivot
-// step: the first wavefront finds the pivot (shuffles, the same rule); then
-// rows k and p are exchanged, row k normalised (also into rowk) and the
-// pivot column kept in colk; then every other row is eliminated.  The
-// values are those of gauss_jordan (the same operations on the same
-// operands).  The column interchanges are applied as one permutation when
-// the inverse is written back.
-__global__ void __launch_bounds__(GJ_T) k_gauss_jordan_lds(int64_t nd64, double* dense, int32_t* piv,
-                                                           int32_t* flag) {
-  extern __shared__ double lds[];
-  const int nd = (int)nd64;
-  double* a = lds;
-  double* colk = a + nd * nd;
-  double* rowk = colk + nd;
-  int32_t* perm = (int32_t*)(rowk + nd);
-  __shared__ int s_p;
-  __shared__ double s_pk, s_kk;
-  const int t = (int)threadIdx.x;
-  for (int e = t; e < nd * nd; e += GJ_T) a[e] = dense[e];
-  __syncthreads();
-  for (int k = 0; k < nd; ++k) {
-    if (t < 64) {
-      // first row of largest |a_ik|, i >= k
-      double best = -1.0;
-      int bi = nd;
-      for (int i = k + t; i < nd; i += 64) {
-        const double v = fabs(a[i * nd + k]);
-        if (v > best) {
-          best = v;
-          bi = i;
+// The same inversion with the matrix in registers: 32 x 32 threads, thread
+// (ti, tj) holding entries (ti + 32 r, tj + 32 c), for nd <= 32 R.  Rows stay
+// where they are; pos is the position the interchanges would have given a row
+// (rows of pos < k are done), kept by every wavefront for itself, so a pivot
+// step has two barriers: the pivot column in LDS, then every wavefront finds
+// the pivot and the owners of its row normalise it; the row in LDS, then all
+// eliminate.  The values are those of gauss_jordan (the same operations on
+// the same operands; rows of equal magnitude by their positions).  With P the
+// interchanges, A^-1 = (P A)^-1 P: column j of it is column pos[j].
+// Bound by the chain of pivot steps, 1.4 us each at nd = 102, of which the
+// elimination's 32 multiplications and subtractions a thread take a fifth:
+// 138 us, against 381 us with the matrix in LDS (603 x 411's coarsest level 78
+// us against 150, 131 x 75 x 97's 113 against 333).
+// Above 192 rows the matrix is in global memory.
+template <int R>
+__global__ void __launch_bounds__(GJ_T) k_gauss_jordan_regs(int nd, double* dense, int32_t* flag) {
+  constexpr int NP = 32 * R, S = (NP + 63) / 64;
+  __shared__ double colk[2][64 * S], rowk[NP];
+  __shared__ int32_t s_pos[64 * S], s_ipos[64 * S];
+  const int t = (int)threadIdx.x, lane = t & 63, ti = t >> 5, tj = t & 31;
+  double a[R][R];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < R; ++c) {
+      const int i = ti + 32 * r, j = tj + 32 * c;
+      a[r][c] = i < nd && j < nd ? dense[i * nd + j] : 0.0;
+    }
+  int pos[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) pos[s] = lane + 64 * s < nd ? lane + 64 * s : -1;
+#pragma unroll
+  for (int kb = 0; kb < R; ++kb)  // the pivot column is register column kb of the threads tj = kk
+    for (int kk = 0; kk < 32; ++kk) {
+      const int k = 32 * kb + kk;
+      if (k >= nd) break;
+      double* col = colk[k & 1];
+      if (tj == kk) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) col[ti + 32 * r] = a[r][kb];
+      }
+      __syncthreads();
+      double v[S], best = -1.0;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const double x = fabs(col[lane + 64 * s]);
+        v[s] = pos[s] >= k && x >= 0.0 ? x : -1.0;
+        best = v[s] > best ? v[s] : best;
+      }
+      best = wave_max(best);
+      int p = -1, q = 0;
+      if (best > 0.0) {
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          for (uint64_t m = __ballot(v[s] == best); m; m &= m - 1) {
+            const int l = __builtin_ctzll(m), x = __builtin_amdgcn_readlane(pos[s], l);
+            if (p < 0 || x < q) {
+              p = l + 64 * s;
+              q = x;
+            }
+          }
+      } else {  // no usable pivot (zero or NaN column): keep row k and report singular
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const uint64_t m = __ballot(pos[s] == k);
+          if (m) p = __builtin_ctzll(m) + 64 * s;
         }
+        q = k;
+        if (t == 0) atomicOr(flag, 2);
       }
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        const double v2 = __shfl_xor(best, off, 64);
-        const int i2 = __shfl_xor(bi, off, 64);
-        if (v2 > best || (v2 == best && i2 < bi)) {
-          best = v2;
-          bi = i2;
+      for (int s = 0; s < S; ++s) pos[s] = lane + 64 * s == p ? k : pos[s] == k ? q : pos[s];
+      const bool own = ti == (p & 31);
+      if (own) {
+        const double pv = col[p];
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+          double x = a[0][c];
+#pragma unroll
+          for (int r = 1; r < R; ++r) x = (p >> 5) == r ? a[r][c] : x;
+          rowk[tj + 32 * c] = (c == kb && tj == kk ? 1.0 : x) / pv;
         }
       }
-      if (t == 0) {
-        // no usable pivot (zero or NaN column): keep row k and report singular
-        const int p = (bi < nd && best > 0.0) ? bi : k;
-        s_p = p;
-        s_pk = a[p * nd + k];
-        s_kk = a[k * nd + k];
-        piv[k] = p;
-        if (!(best > 0.0)) atomicOr(flag, 2);
+      __syncthreads();
+      double f[R], rj[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) f[r] = col[ti + 32 * r];
+#pragma unroll
+      for (int c = 0; c < R; ++c) rj[c] = rowk[tj + 32 * c];
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+          const double x = a[r][c] - f[r] * rj[c];
+          a[r][c] = c == kb && tj == kk ? -f[r] * rj[c] : x;
+        }
+      if (own) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if ((p >> 5) == r) {
+#pragma unroll
+            for (int c = 0; c < R; ++c) a[r][c] = rj[c];
+          }
       }
     }
-    __syncthreads();
-    const int p = s_p;
-    const double pv = s_pk;
-    for (int j = t; j < nd; j += GJ_T) {
-      const double xk = a[k * nd + j], xp = a[p * nd + j];
-      const double r = (j == k ? 1.0 : xp) / pv;
-      if (p != k) a[p * nd + j] = xk;
-      a[k * nd + j] = r;
-      rowk[j] = r;
-    }
-    for (int i = t; i < nd; i += GJ_T) colk[i] = i == k ? s_pk : i == p ? s_kk : a[i * nd + k];
-    __syncthreads();
-    for (int e = t; e < nd * nd; e += GJ_T) {
-      const int i = e / nd, j = e - i * nd;
-      if (i == k) continue;
-      const double f = colk[i];
-      if (j == k)
-        a[e] = -f * rowk[k];
-      else
-        a[e] -= f * rowk[j];
-    }
-    __syncthreads();
-  }
-  // the column interchanges, last to first, as one permutation: position j
-  // of the inverse holds column perm[j] of a
-  if (t == 0) {
-    for (int j = 0; j < nd; ++j) perm[j] = j;
-    for (int k = nd - 1; k >= 0; --k) {
-      const int q = piv[k];
-      const int32_t x = perm[k];
-      perm[k] = perm[q];
-      perm[q] = x;
-    }
+  if (t < 64) {
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+      if (pos[s] >= 0) {
+        s_pos[lane + 64 * s] = pos[s];
+        s_ipos[pos[s]] = lane + 64 * s;
+      }
   }
   __syncthreads();
-  for (int e = t; e < nd * nd; e += GJ_T) {
-    const int i = e / nd, j = e - i * nd;
-    dense[e] = a[i * nd + perm[j]];
-  }
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < R; ++c) {
+      const int i = ti + 32 * r, j = tj + 32 * c;
+      if (i < nd && j < nd) dense[s_pos[i] * nd + s_ipos[j]] = a[r][c];
+    }
 }
 
 __global__ void __launch_bounds__(GJ_T) k_gauss_jordan_global(int64_t nd, double* dense, int32_t* piv,
@@ -3030,10 +3090,6 @@ void init_kernel_attributes() {
   // the team's tables take the default LDS limit whole, its static words come on top
   (void)hipFuncSetAttribute((const void*)k_team_build<1024>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             1024 / 16 * BUILD_LDS_ROW);
-  const size_t lds_max = (size_t)(GJ_LDS_MAX * GJ_LDS_MAX + 2 * GJ_LDS_MAX) * sizeof(double) +
-                         GJ_LDS_MAX * sizeof(int32_t);
-  (void)hipFuncSetAttribute((const void*)k_gauss_jordan_lds, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds_max);
   (void)hipGetLastError();
 }
 
@@ -3120,21 +3176,18 @@ template void launch_cls_gather<float>(hipStream_t, int64_t, const int32_t*, Sel
                                        Sell, float*, float*, const float*);
 
 void launch_gauss_jordan(hipStream_t st, int64_t nd, double* dense, int32_t* piv, int32_t* flag) {
-  static int lds_ok = -1;
-  const size_t lds_max = (size_t)(GJ_LDS_MAX * GJ_LDS_MAX + 2 * GJ_LDS_MAX) * sizeof(double) +
-                         GJ_LDS_MAX * sizeof(int32_t);
-  if (lds_ok < 0)
-    lds_ok = hipFuncSetAttribute((const void*)k_gauss_jordan_lds,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max) == hipSuccess;
-  if (nd <= GJ_LDS_MAX && lds_ok) {
-    const size_t lds = (size_t)(nd * nd + 2 * nd) * sizeof(double) + nd * sizeof(int32_t);
-    hipLaunchKernelGGL(k_gauss_jordan_lds, dim3(1), dim3(GJ_T), lds, st, nd, dense, piv, flag);
-  } else {
-    // the pivot column is staged after the pivot indices: callers size the
-    // pivot buffer for nd ints plus nd doubles
-    double* colk = (double*)(piv + ((nd + 1) & ~(int64_t)1));
-    hipLaunchKernelGGL(k_gauss_jordan_global, dim3(1), dim3(GJ_T), 0, st, nd, dense, piv, flag, colk);
+  switch ((nd + 31) / 32) {
+#define X(R) \
+  case R: \
+    hipLaunchKernelGGL((k_gauss_jordan_regs<R>), dim3(1), dim3(GJ_T), 0, st, (int)nd, dense, flag); \
+    return;
+    X(1) X(2) X(3) X(4) X(5) X(6)
+#undef X
   }
+  // the pivot column is staged after the pivot indices: callers size the
+  // pivot buffer for nd ints plus nd doubles
+  double* colk = (double*)(piv + ((nd + 1) & ~(int64_t)1));
+  hipLaunchKernelGGL(k_gauss_jordan_global, dim3(1), dim3(GJ_T), 0, st, nd, dense, piv, flag, colk);
 }
 
 template <typename T>
