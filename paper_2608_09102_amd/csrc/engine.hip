@@ -973,7 +973,7 @@ void allocate_numeric(llg_ctx& c, Arena& ar) {
     c.lv[1].xp = ar.get(ts * 3 * c.lv[1].A.n, true);  // level-1 iterate with the prolonged correction
   }
   // partial sums: up to 2R+3 columns of the delayed Gram-Schmidt dots (R+2 for the two-pass form)
-  c.part = ar.lazy<double>(std::max<int64_t>(std::max<int64_t>((2 * R + 4) * c.npart_vec, c.npart_rows), kparts) + 64);
+  c.part = ar.lazy<double>(std::max<int64_t>(std::max<int64_t>((2 * R + 4) * std::max<int64_t>(c.npart_vec, TEAM_W), c.npart_rows), kparts) + 64);
   c.ks.H = ar.lazy<double>((R + 1) * R);
   c.ks.cs = ar.lazy<double>(R);
   c.ks.sn = ar.lazy<double>(R);
@@ -1945,6 +1945,11 @@ void iter_arnoldi(llg_ctx& c, int j) {
   if (c.opts.arnoldi == LLG_ARNOLDI_DCGS2) {
     // delayed reorthogonalization: one sweep for the dots, one for v_j and w'
     double* u = c.V + (int64_t)j * c.ld;
+    if (m <= ARNOLDI_TEAM) {
+      launch_dcgs_team(st, c.team_st, c.team_xcd, m, j, c.V, c.ld, u, c.w, u + c.ld, c.part, R, c.ks, c.host);
+      LCHK();
+      return;
+    }
     launch_dcgs_dots(st, m, j, c.V, c.ld, u, c.w, c.part);
     launch_dcgs_finish1(st, c.part, dots_blocks(m, j), j, R, c.ks);
     launch_dcgs_update(st, m, j, c.V, c.ld, c.ks.coef, u, c.w, c.V + (int64_t)(j + 1) * c.ld, c.part);

@@ -638,6 +638,13 @@ void launch_dcgs_update(hipStream_t st, int64_t m, int nv, const double* V, int6
                         double* u, const double* w, double* wo, double* part);
 void launch_dcgs_finish2(hipStream_t st, const double* part, int64_t nparts, int j, int R, KrylovScalars ks,
                          double* host);
+// The whole orthogonalization of iteration j by a team, for vectors of at most
+// ARNOLDI_TEAM entries; part holds (2 R + 4) TEAM_W sums.  Above, the one XCD's
+// share of the memory system costs more than the launches: an iteration by the
+// team / by four kernels 35.4 / 39.2 us at 27648 entries, 42.2 / 39.4 at 36000.
+constexpr int64_t ARNOLDI_TEAM = 30720;
+void launch_dcgs_team(hipStream_t st, TeamState* ts, int pick, int64_t m, int j, const double* V, int64_t ldv,
+                      double* u, const double* w, double* wo, double* part, int R, KrylovScalars ks, double* host);
 void launch_dcgs_last(hipStream_t st, const double* part, int64_t nparts, int k, int R, KrylovScalars ks,
                       double* host);
 void launch_solve_y(hipStream_t st, int k, int R, KrylovScalars ks);
