@@ -1457,7 +1457,6 @@ void setup_values(llg_ctx& c, const double* m, const double* mprev, const double
     GalSrc<T> src;
     src.fval = (const T*)L.val;
     src.fvt = (const T*)L.vt;
-    src.fk = (const T*)L.kf;
     src.knm = (const T*)L.knm;  // factored grid level: K node-major
     src.frp = L.brp;
     src.fci = L.bci;

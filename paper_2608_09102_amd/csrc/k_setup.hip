@@ -2019,248 +2019,53 @@ __global__ void k_fact_blocks(int nx, int ny, int nz, double inv_h2, const doubl
 }
 
 // ---------------------------------------------------------------- Galerkin
-// The fine block (i, j) of a Galerkin sum, in FP64.  Factored grid level: the
-// identity on the diagonal, else K_i, read from the node-major copy the
-// assembly writes (nine contiguous values) or from fk.  Other levels: the
-// slot-ordered copy (nine contiguous values) when there is one, else the
-// sliced-ELL values.
-template <typename T, bool FACT>
-__device__ inline void fine_block(const GalSrc<T>& g, int32_t i, int32_t j, int64_t k, int64_t fs, int fl,
-                                  int64_t fb, int u, double* f) {
-  if (FACT) {
-    if (j == i) {
+// K_i of grid row i, and (BSR) its diagonal block, at slot dp of the row.
+template <typename T, bool BSR>
+__device__ inline void grid_row_blocks(const GalSrc<T>& g, const int32_t* __restrict__ fsl, int32_t i, int dp, T* k,
+                                       T* d) {
+  if constexpr (BSR) {
+    const int32_t fs = i / SL;
+    const T* v = g.fval + (int64_t)fsl[fs] * 9 + (i - fs * SL);
 #pragma unroll
-      for (int e = 0; e < 9; ++e) f[e] = (e == 0 || e == 4 || e == 8) ? 1.0 : 0.0;
-    } else if (g.knm) {
-#pragma unroll
-      for (int e = 0; e < 9; ++e) f[e] = (double)g.knm[9 * (int64_t)i + e];
-    } else {
-      const int64_t kb = fs * 9 * SL + fl;
-#pragma unroll
-      for (int e = 0; e < 9; ++e) f[e] = (double)g.fk[kb + e * SL];
+    for (int e = 0; e < 9; ++e) {
+      k[e] = v[(dp == 0 ? 9 : 0) * SL + e * SL];
+      d[e] = v[(int64_t)dp * 9 * SL + e * SL];
     }
-  } else if (g.fvt) {
-#pragma unroll
-    for (int e = 0; e < 9; ++e) f[e] = (double)g.fvt[k * 9 + e];
   } else {
-    const int64_t vb = fb * 9 + (int64_t)u * 9 * SL + fl;
 #pragma unroll
-    for (int e = 0; e < 9; ++e) f[e] = (double)g.fval[vb + e * SL];
+    for (int e = 0; e < 9; ++e) k[e] = g.knm[9 * (int64_t)i + e];
   }
 }
 
-// Large coarse levels: one workgroup per slice of the coarse matrix; a thread
-// takes GC consecutive block slots (row l, slots t..t+GC-1) of the slice, so
-// that one walk over the fine rows of the members serves GC coarse blocks.
-// Block (I, J) is the sum, over the members i of aggregate I in ascending
-// order and over the stored blocks (i, j) of row i in ascending j with
-// agg(j) = J, of the fine block a_ij (eq. Ac_direct), accumulated in FP64
-// starting from zero.  The inverse of a diagonal block is computed from the
-// stored (rounded) block.
-constexpr int GC = 4;
-template <typename T, bool FACT>
-__global__ void __launch_bounds__(TPB) k_galerkin_slices(int64_t nc, const int32_t* __restrict__ csl, const int32_t* __restrict__ ccol,
-                           T* __restrict__ cval, T* __restrict__ cdinv, const int32_t* __restrict__ mptr,
-                           const int32_t* __restrict__ mem, const int32_t* __restrict__ fsl,
-                           const int32_t* __restrict__ fcol, const int32_t* __restrict__ agg, const GalSrc<T> g) {
-  // XCD-contiguous slices: neighbouring aggregates read the same fine rows
-  const int64_t s = xcd_block(blockIdx.x, gridDim.x);
-  const int64_t cb = csl[s];
-  const int width = (int)((csl[s + 1] - cb) / SL);
-  const int nchunk = (width + GC - 1) / GC;
-  // Grid level stored per node: the member rows of the slice's coarse rows
-  // (up to GM members per row) are staged in LDS once, their entries'
-  // aggregates, the diagonal's position and K_i, and every slot group of a
-  // coarse row reads them there (a row's slot groups would otherwise gather
-  // the same aggregates from L2 once each).
-  constexpr int GM = 4;
-  __shared__ int32_t s_aa[SL * GM * 8];
-  __shared__ int32_t s_dp[SL * GM];
-  __shared__ int32_t s_nm[SL];
-  __shared__ T s_k[SL * GM * 9];
-  if (FACT && g.knm) {
-    for (int tt = threadIdx.x; tt < SL * GM; tt += blockDim.x) {
-      const int lr = tt / GM, m = tt - lr * GM;
-      const int64_t I = s * SL + lr;
-      int32_t nm = 0;
-      if (I < nc) {
-        const int32_t q0 = mptr[I];
-        nm = mptr[I + 1] - q0;
-        if (m < nm && nm <= GM) {
-          const int32_t i = mem[q0 + m];
-          const int32_t k0 = g.frp[i], len = min(g.frp[i + 1] - k0, 8);
-          int dp = -1;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int32_t j = k < len ? g.fci[k0 + k] : -1;
-            s_aa[(lr * GM + m) * 8 + k] = j >= 0 ? agg[j] : -1;
-            dp = j == i ? k : dp;
-          }
-          s_dp[lr * GM + m] = dp;
-#pragma unroll
-          for (int e = 0; e < 9; ++e) s_k[(lr * GM + m) * 9 + e] = g.knm[9 * (int64_t)i + e];
-        }
-      }
-      if (m == 0) s_nm[lr] = nm;
-    }
-    __syncthreads();
-  }
-  for (int k = threadIdx.x; k < nchunk * SL; k += blockDim.x) {
-    const int c = k / SL, l = k - c * SL;
-    const int64_t I = s * SL + l;
-    if (I >= nc) continue;
-    int32_t J[GC];
-#pragma unroll
-    for (int h = 0; h < GC; ++h) {
-      const int t = c * GC + h;
-      J[h] = t < width ? ccol[cb + (int64_t)t * SL + l] : -1;
-    }
-    bool any = false;
-#pragma unroll
-    for (int h = 0; h < GC; ++h) any = any || J[h] >= 0;
-    if (!any) continue;  // padding only
-    double acc[GC][9];
-#pragma unroll
-    for (int h = 0; h < GC; ++h)
-#pragma unroll
-      for (int e = 0; e < 9; ++e) acc[h][e] = 0.0;
-    if (FACT && g.knm) {
-      // Grid-level rows (at most 8 entries): every block of row i is K_i but
-      // the diagonal one, I.  So the entries of the row that fall into slot h
-      // are taken from a bit mask, in ascending order, and each costs one
-      // block addition; the FP64 sums are those of the walk below.
-      auto add_member = [&](const int32_t* aa, int dpos, const double* kd) {
-#pragma unroll
-        for (int h = 0; h < GC; ++h) {
-          unsigned m = 0;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) m |= (J[h] >= 0 && aa[k] == J[h]) ? 1u << k : 0u;
-          while (m) {
-            const int k = __ffs(m) - 1;
-            m &= m - 1;
-            const bool d = k == dpos;
-#pragma unroll
-            for (int e = 0; e < 9; ++e) acc[h][e] += d ? ((e == 0 || e == 4 || e == 8) ? 1.0 : 0.0) : kd[e];
-          }
-        }
-      };
-      const int nm = s_nm[l];
-      if (nm <= GM) {
-        for (int m = 0; m < nm; ++m) {
-          const int b = l * GM + m;
-          int32_t aa[8];
-          double kd[9];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) aa[k] = s_aa[b * 8 + k];
-#pragma unroll
-          for (int e = 0; e < 9; ++e) kd[e] = (double)s_k[b * 9 + e];
-          add_member(aa, s_dp[b], kd);
-        }
-      } else {
-        for (int32_t q = mptr[I]; q < mptr[I + 1]; ++q) {
-          const int32_t i = mem[q];
-          const int32_t k0 = g.frp[i], len = min(g.frp[i + 1] - k0, 8);
-          int32_t aa[8];
-          int dpos = -1;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int32_t j = k < len ? g.fci[k0 + k] : -1;
-            aa[k] = j >= 0 ? agg[j] : -1;
-            dpos = j == i ? k : dpos;
-          }
-          double kd[9];
-#pragma unroll
-          for (int e = 0; e < 9; ++e) kd[e] = (double)g.knm[9 * (int64_t)i + e];
-          add_member(aa, dpos, kd);
-        }
-      }
-    } else {
-      for (int32_t q = mptr[I]; q < mptr[I + 1]; ++q) {
-        const int32_t i = mem[q];
-        const int64_t fs = i / SL;
-        const int fl = i - (int)(fs * SL);
-        const int64_t fb = (FACT || g.fvt) ? 0 : fsl[fs];  // sliced fine values only
-        // the member's row in CSR order (contiguous columns and, on coarse
-        // levels, contiguous blocks), four at a time: their column and
-        // aggregate loads are in flight together; the blocks are still added
-        // in ascending column order
-        const int32_t k0 = g.frp[i], k1 = g.frp[i + 1];
-        for (int32_t kb = k0; kb < k1; kb += 4) {
-          int32_t jj[4], aa[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) jj[k] = kb + k < k1 ? g.fci[kb + k] : -1;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) aa[k] = jj[k] >= 0 ? agg[jj[k]] : -1;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            int hit = -1;
-#pragma unroll
-            for (int h = 0; h < GC; ++h) hit = aa[k] >= 0 && aa[k] == J[h] ? h : hit;
-            if (hit < 0) continue;
-            double f[9];
-            fine_block<T, FACT>(g, i, jj[k], kb + k, fs, fl, fb, kb + k - k0, f);
-#pragma unroll
-            for (int h = 0; h < GC; ++h)
-              if (h == hit)
-#pragma unroll
-                for (int e = 0; e < 9; ++e) acc[h][e] += f[e];
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < GC; ++h) {
-      if (J[h] < 0) continue;
-      const int t = c * GC + h;
-      const int64_t vb = cb * 9 + (int64_t)t * 9 * SL + l;
-      T stv[9];
-#pragma unroll
-      for (int e = 0; e < 9; ++e) stv[e] = (T)acc[h][e];
-      if (cval) {
-#pragma unroll
-        for (int e = 0; e < 9; ++e) cval[vb + e * SL] = stv[e];
-      }
-      if (g.cvt) {
-        // CSR-ordered copy for the next level's product, which walks member rows
-        const int64_t pos = (int64_t)g.crp[I] + t;
-#pragma unroll
-        for (int e = 0; e < 9; ++e) g.cvt[pos * 9 + e] = stv[e];
-      }
-      if (J[h] == (int32_t)I) {
-        double D[9], Di[9];
-#pragma unroll
-        for (int e = 0; e < 9; ++e) D[e] = (double)stv[e];
-        inv3(D, Di);
-        const int64_t db = s * 9 * SL + l;
-#pragma unroll
-        for (int e = 0; e < 9; ++e) cdinv[db + e * SL] = (T)Di[e];
-      }
-    }
-  }
-}
-
-// Level 1 of a grid level stored per node, one thread per coarse block in
-// the coarse level's CSR order: a workgroup takes a slice of 64 coarse rows,
-// stages their members' rows once in LDS (each entry's aggregate, the
-// diagonal's position and K_i; up to GM members per row, larger aggregates
-// walk their rows from memory), and its threads take the slice's blocks in
-// order, so the CSR-ordered copy is written by consecutive threads.  Block
-// (I, J) sums, over the members of I in ascending order and over the entries
-// of each member's row in ascending order whose aggregate is J, the fine
-// block: the identity on the diagonal, K_i elsewhere (eq. Ac_direct), in
-// FP64 from zero, as k_galerkin_slices does.
-template <typename T>
+// Level 1, from the grid level: one thread per coarse block in the coarse
+// level's CSR order.  A workgroup takes a slice of 64 coarse rows, stages
+// their members' rows once in LDS (each entry's aggregate, the diagonal's
+// position and K_i; up to GM members per row, larger aggregates walk their
+// rows from memory), and its threads take the slice's blocks in order, so the
+// CSR-ordered copy is written by consecutive threads.  Block (I, J) sums, over
+// the members of I in ascending order and over the entries of each member's
+// row in ascending order whose aggregate is J, the fine block: a grid row has
+// one block K_i off the diagonal (and the identity on it, where the rows are
+// scaled), so K_i is read once per node: from the node-major copy of the
+// factored form, or (BSR) from the first off-diagonal slot, with the diagonal
+// block from its own.  (eq. Ac_direct, in FP64 from zero.)
+// Bound by the reads of K_i and the writes of the coarse blocks.  256^3,
+// factored FP32: 1.78 ms, against 5.2 ms row by row and 2.31 ms by groups of
+// slots; 1024^2, BSR FP64: 245 us, against 476 us by groups of slots, which
+// read all five blocks of a row.
+template <typename T, bool BSR, int GM>
 __global__ void __launch_bounds__(TPB) k_galerkin_grid(int64_t nc, const int32_t* __restrict__ csl,
                                                        T* __restrict__ cval, T* __restrict__ cdinv,
                                                        const int32_t* __restrict__ mptr,
                                                        const int32_t* __restrict__ mem,
+                                                       const int32_t* __restrict__ fsl,
                                                        const int32_t* __restrict__ agg, const GalSrc<T> g) {
   const int64_t s = xcd_block(blockIdx.x, gridDim.x);
-  constexpr int GM = 4;
   __shared__ int32_t s_aa[SL * GM * 8];
   __shared__ int32_t s_dp[SL * GM];
   __shared__ int32_t s_nm[SL];
   __shared__ T s_k[SL * GM * 9];
+  __shared__ T s_d[BSR ? SL * GM * 9 : 1];
   __shared__ int32_t s_rs[SL + 1];
   for (int tt = threadIdx.x; tt < SL * GM; tt += blockDim.x) {
     const int lr = tt / GM, m = tt - lr * GM;
@@ -2280,8 +2085,8 @@ __global__ void __launch_bounds__(TPB) k_galerkin_grid(int64_t nc, const int32_t
           dp = j == i ? k : dp;
         }
         s_dp[lr * GM + m] = dp;
-#pragma unroll
-        for (int e = 0; e < 9; ++e) s_k[(lr * GM + m) * 9 + e] = g.knm[9 * (int64_t)i + e];
+        T* kd = s_k + (lr * GM + m) * 9;
+        grid_row_blocks<T, BSR>(g, fsl, i, dp, kd, BSR ? s_d + (lr * GM + m) * 9 : nullptr);
       }
     }
     if (m == 0) s_nm[lr] = nm;
@@ -2307,7 +2112,7 @@ __global__ void __launch_bounds__(TPB) k_galerkin_grid(int64_t nc, const int32_t
     double acc[9];
 #pragma unroll
     for (int e = 0; e < 9; ++e) acc[e] = 0.0;
-    auto add_row = [&](const int32_t* aa, int dpos, const double* kd) {
+    auto add_row = [&](const int32_t* aa, int dpos, const double* kd, const T* dd) {
       unsigned msk = 0;
 #pragma unroll
       for (int k = 0; k < 8; ++k) msk |= aa[k] == J ? 1u << k : 0u;
@@ -2316,7 +2121,7 @@ __global__ void __launch_bounds__(TPB) k_galerkin_grid(int64_t nc, const int32_t
         msk &= msk - 1;
         const bool d = k == dpos;
 #pragma unroll
-        for (int e = 0; e < 9; ++e) acc[e] += d ? ((e == 0 || e == 4 || e == 8) ? 1.0 : 0.0) : kd[e];
+        for (int e = 0; e < 9; ++e) acc[e] += d ? (BSR ? (double)dd[e] : (e == 0 || e == 4 || e == 8) ? 1.0 : 0.0) : kd[e];
       }
     };
     const int nm = s_nm[l];
@@ -2329,7 +2134,7 @@ __global__ void __launch_bounds__(TPB) k_galerkin_grid(int64_t nc, const int32_t
         for (int k = 0; k < 8; ++k) aa[k] = s_aa[b * 8 + k];
 #pragma unroll
         for (int e = 0; e < 9; ++e) kd[e] = (double)s_k[b * 9 + e];
-        add_row(aa, s_dp[b], kd);
+        add_row(aa, s_dp[b], kd, BSR ? s_d + b * 9 : nullptr);
       }
     } else {
       for (int32_t qq = mptr[I]; qq < mptr[I + 1]; ++qq) {
@@ -2343,18 +2148,22 @@ __global__ void __launch_bounds__(TPB) k_galerkin_grid(int64_t nc, const int32_t
           aa[k] = j >= 0 ? agg[j] : -1;
           dpos = j == i ? k : dpos;
         }
+        T kt[9], dt[9];
+        grid_row_blocks<T, BSR>(g, fsl, i, dpos, kt, dt);
         double kd[9];
 #pragma unroll
-        for (int e = 0; e < 9; ++e) kd[e] = (double)g.knm[9 * (int64_t)i + e];
-        add_row(aa, dpos, kd);
+        for (int e = 0; e < 9; ++e) kd[e] = (double)kt[e];
+        add_row(aa, dpos, kd, dt);
       }
     }
     T stv[9];
 #pragma unroll
     for (int e = 0; e < 9; ++e) stv[e] = (T)acc[e];
     const int64_t pos = (int64_t)p0 + q;
+    if (g.cvt) {
 #pragma unroll
-    for (int e = 0; e < 9; ++e) g.cvt[pos * 9 + e] = stv[e];
+      for (int e = 0; e < 9; ++e) g.cvt[pos * 9 + e] = stv[e];
+    }
     if (cval) {
       const int64_t vb = cb * 9 + (int64_t)t * 9 * SL + l;
 #pragma unroll
@@ -2381,7 +2190,7 @@ __global__ void __launch_bounds__(TPB) k_galerkin_grid(int64_t nc, const int32_t
 // entry's aggregate adds it.  So every block (I, J) is the sum, over the
 // members i of I in ascending order and over the stored blocks (i, j) of row i
 // in ascending j with agg(j) = J, of a_ij (eq. Ac_direct), accumulated in FP64
-// from zero, as in the other two kernels, while each fine row is read once per
+// from zero, as from the grid level, while each fine row is read once per
 // coarse row (not once per group of slots) and with contiguous loads.
 constexpr int GR_L = 16;
 template <typename T>
@@ -2482,76 +2291,6 @@ __global__ void __launch_bounds__(TPB) k_galerkin_rows(int64_t nc, const int32_t
         for (int x = 0; x < 9; ++x) cdinv[db + x * SL] = (T)Di[x];
       }
     }
-  }
-}
-
-// Small coarse levels (few slices): one thread per block slot (I, J), its
-// slice found by bisection.  The block is the sum, over the
-// members i of aggregate I in ascending order and over the stored blocks
-// (i, j) of row i in ascending j with agg(j) = J, of the fine block a_ij
-// (eq. Ac_direct), accumulated in FP64 starting from zero.  The inverse of a
-// diagonal block is computed from the stored (rounded) block.
-template <typename T, bool FACT>
-__global__ void k_galerkin_slots(int64_t nc, int64_t ns, const int32_t* __restrict__ csl,
-                           const int32_t* __restrict__ ccol, T* __restrict__ cval, T* __restrict__ cdinv,
-                           const int32_t* __restrict__ mptr, const int32_t* __restrict__ mem,
-                           const int32_t* __restrict__ fsl, const int32_t* __restrict__ fcol,
-                           const int32_t* __restrict__ agg, const GalSrc<T> g) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= csl[ns]) return;
-  // slice of slot p: the last s with csl[s] <= p
-  int64_t lo = 0, hi = ns - 1;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi + 1) >> 1;
-    if (csl[mid] <= p)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  const int64_t s = lo, cb = csl[s];
-  const int t = (int)((p - cb) / SL), l = (int)((p - cb) % SL);
-  const int64_t I = s * SL + l;
-  const int32_t J = ccol[p];
-  if (J < 0 || I >= nc) return;
-  double acc[9];
-#pragma unroll
-  for (int e = 0; e < 9; ++e) acc[e] = 0.0;
-  for (int32_t q = mptr[I]; q < mptr[I + 1]; ++q) {
-    const int32_t i = mem[q];
-    const int64_t fs = i / SL;
-    const int fl = i - (int)(fs * SL);
-    const int64_t fb = (FACT || g.fvt) ? 0 : fsl[fs];  // sliced fine values only
-    const int32_t k0 = g.frp[i], k1 = g.frp[i + 1];
-    for (int32_t k = k0; k < k1; ++k) {
-      const int32_t j = g.fci[k];
-      if (agg[j] != J) continue;
-      double f[9];
-      fine_block<T, FACT>(g, i, j, k, fs, fl, fb, k - k0, f);
-#pragma unroll
-      for (int e = 0; e < 9; ++e) acc[e] += f[e];
-    }
-  }
-  const int64_t vb = cb * 9 + (int64_t)t * 9 * SL + l;
-  T st[9];
-#pragma unroll
-  for (int e = 0; e < 9; ++e) st[e] = (T)acc[e];
-  if (cval) {
-#pragma unroll
-    for (int e = 0; e < 9; ++e) cval[vb + e * SL] = st[e];
-  }
-  if (g.cvt) {
-    const int64_t pos = (int64_t)g.crp[I] + t;
-#pragma unroll
-    for (int e = 0; e < 9; ++e) g.cvt[pos * 9 + e] = st[e];
-  }
-  if (J == (int32_t)I) {
-    double D[9], Di[9];
-#pragma unroll
-    for (int e = 0; e < 9; ++e) D[e] = (double)st[e];
-    inv3(D, Di);
-    const int64_t db = s * 9 * SL + l;
-#pragma unroll
-    for (int e = 0; e < 9; ++e) cdinv[db + e * SL] = (T)Di[e];
   }
 }
 
@@ -3097,33 +2836,23 @@ template <typename T>
 void launch_galerkin(hipStream_t st, Sell C, T* cval, T* cdinv, const int32_t* mptr, const int32_t* mem, Sell F,
                      const int32_t* agg, const GalSrc<T>& g) {
   if (C.n <= 0) return;
-#define LLG_GAL(FACT)                                                                                          \
-  if (C.nslices >= 1024)                                                                                       \
-    hipLaunchKernelGGL((k_galerkin_slices<T, FACT>), dim3((unsigned)C.nslices), dim3(TPB), 0, st, C.n, C.sl_ptr, \
-                       C.col, cval, cdinv, mptr, mem, F.sl_ptr, F.col, agg, g);                                  \
-  else                                                                                                         \
-    hipLaunchKernelGGL((k_galerkin_slots<T, FACT>), dim3(nblk(C.nslots)), dim3(TPB), 0, st, C.n, C.nslices,      \
-                       C.sl_ptr, C.col, cval, cdinv, mptr, mem, F.sl_ptr, F.col, agg, g)
   // the coarse levels of a coarse level row by row, from its CSR-ordered copy
   // (also the small ones: 24-71 us against 50-310 us by slot, one thread and
-  // one slice bisection each, at 1,000-32,000 rows).  Level 1 of a grid level
-  // stored per node block by block, a thread per block in CSR order (row by
-  // row it measured 5.2 ms at 256^3, by slot groups 2.31 ms, block by block
-  // 1.78 ms: its blocks come from K_i, one load per member).
-  const bool rows = g.crp && g.cci && !g.fk && g.fvt != nullptr;
-  const dim3 rg(nblk(C.n, TPB / GR_L)), rt(TPB);
-  if (rows) {
+  // one slice bisection each, at 1,000-32,000 rows), level 1 block by block
+  // (its blocks come from K_i, one load per member); room for eight members a
+  // row where the mean is above four (three passes)
+  const dim3 rg(nblk(C.n, TPB / GR_L)), rt(TPB), sg((unsigned)C.nslices);
+  if (g.fvt)
     hipLaunchKernelGGL((k_galerkin_rows<T>), rg, rt, 0, st, C.n, C.sl_ptr, cval, cdinv, mptr, mem, agg, g);
-  } else if (g.fk && g.knm && g.crp && g.cci && g.cvt) {
-    // level 1 of the per-node grid level, block by block in CSR order
-    hipLaunchKernelGGL((k_galerkin_grid<T>), dim3((unsigned)C.nslices), rt, 0, st, C.n, C.sl_ptr, cval, cdinv, mptr,
-                       mem, agg, g);
-  } else if (g.fk) {
-    LLG_GAL(true);
-  } else {
-    LLG_GAL(false);
-  }
-#undef LLG_GAL
+  else if (g.knm)
+    hipLaunchKernelGGL((k_galerkin_grid<T, false, 4>), sg, rt, 0, st, C.n, C.sl_ptr, cval, cdinv, mptr, mem, F.sl_ptr,
+                       agg, g);
+  else if (F.n <= 4 * C.n)
+    hipLaunchKernelGGL((k_galerkin_grid<T, true, 4>), sg, rt, 0, st, C.n, C.sl_ptr, cval, cdinv, mptr, mem, F.sl_ptr,
+                       agg, g);
+  else
+    hipLaunchKernelGGL((k_galerkin_grid<T, true, 8>), sg, rt, 0, st, C.n, C.sl_ptr, cval, cdinv, mptr, mem, F.sl_ptr,
+                       agg, g);
 }
 template void launch_galerkin<double>(hipStream_t, Sell, double*, double*, const int32_t*, const int32_t*, Sell,
                                       const int32_t*, const GalSrc<double>&);

@@ -320,8 +320,7 @@ template <typename T>
 struct GalSrc {
   const T* fval = nullptr;     // fine blocks, sliced ELL (the grid level stored as BSR)
   const T* fvt = nullptr;      // fine blocks in the fine level's CSR order (coarse levels)
-  const T* fk = nullptr;
-  const T* knm = nullptr;
+  const T* knm = nullptr;      // the factored grid level's off-diagonal block, nine contiguous values a node
   const int32_t* frp = nullptr;  // fine CSR pattern: row pointers and ascending columns
   const int32_t* fci = nullptr;
   T* cvt = nullptr;            // coarse blocks in the coarse level's CSR order (for the next product)
