@@ -355,19 +355,22 @@ PERMALLOY = dict(eps=1.3e-11 / (MU0_MS2 * 1e-12), q=100.0 / MU0_MS2, h_ext=(0.01
 
 def stray_bytes(n, pdims) -> float:
     """Algorithmic HBM bytes of one stray-field evaluation as the library does
-    it: m~ packed into two complex planes on the n-box; forward line passes
-    that read only lines holding data and write the padded extent; the
-    product with the 6 real tensor planes (read 2 planes, write 2 planes);
-    inverse passes that write only the n-box; the cropped output."""
+    it: m read and h written (24 bytes a node each); the two complex planes,
+    of which the second holds the columns kx <= px / 2, written by the x pass
+    over the rows that hold data, transformed along y both ways (3D), taken
+    through the last axis and read by the last x pass; the real tensor's
+    octant read once (six planes, four in 2D)."""
     nx, ny, nz = n
     px, py, pz = pdims
-    N, P = nx * ny * nz, px * py * pz
-    c = 16.0 * 2  # one complex value in each of the two planes
-    passes = [(N, px * ny * nz), (px * ny * nz, px * py * nz)]  # forward x, y: (read, write)
-    if pz > 1:
-        passes.append((px * py * nz, P))
-    fwd = sum(r + w for r, w in passes)
-    return (24.0 * N + c * N) + 2 * c * fwd + (c * P + 48.0 * P + c * P) + (c * N + 24.0 * N)
+    cols = px + px // 2 + 1  # of the two planes
+    rows = cols * ny * nz
+    total = 48.0 * nx * ny * nz + 16.0 * 2 * rows  # the x passes
+    if nz > 1:
+        total += 16.0 * 2 * cols * (ny + py) * nz + 16.0 * 2 * cols * py * nz
+        total += 48.0 * (px // 2 + 1) * (py // 2 + 1) * (pz // 2 + 1)
+    else:
+        total += 16.0 * 2 * rows + 32.0 * (px // 2 + 1) * (py // 2 + 1)
+    return total
 
 
 def field_bench(a, llg, torch, w, form: str, kdepth: int):

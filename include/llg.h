@@ -161,11 +161,12 @@ typedef struct {
   int32_t stray_field;  /* 1: reserve the stray-field workspace (zero-padded FFT grids and the
                            transformed demagnetizing tensor) for llg_step_field; 2*n-1 padded to a
                            power of two must stay <= 4096 per axis (else UNSUPPORTED) */
-  int32_t tail_nodes;   /* block-Jacobi cycles: the coarse levels below the K-cycle levels (and
-                           below level 1 when it is applied through the grid level), each of at
-                           most this many nodes, run their whole V-cycle in one workgroup with
-                           the level vectors on chip (same arithmetic, one launch instead of
-                           three per level); 0 switches it off */
+  int32_t tail_nodes;   /* above 0: the small coarse levels (a matrix of at most 2 MB) run their
+                           whole cycle in one launch of a team of workgroups on one XCD; where
+                           that does not apply (deep K-cycles), block-Jacobi levels below the
+                           K-cycle levels (and below level 1 when it is applied through the grid
+                           level), each of at most this many nodes, run their V-cycle in one
+                           workgroup.  Same arithmetic in both.  0: level by level */
   int32_t pipeline;     /* 1: FGMRES enqueues the preconditioner and product of the next
                            iteration before the host tests the current one's residual
                            estimate (skipped where convergence is predicted); 0: off */
