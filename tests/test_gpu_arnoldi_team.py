@@ -56,3 +56,27 @@ def test_arnoldi_team(gpu, n, krylov, restart, dt):
     say("  iters", res[0][1], res[1][1], "diff %.2e" % d)
     assert d <= 1e-9
     assert abs(res[0][1] - res[1][1]) <= 1 + res[1][1] // restart
+
+
+@pytest.mark.parametrize("n", [(3, 2, 1), (13, 5, 1), (64, 1, 1), (33, 31, 1), (9, 8, 7)],
+                         ids=lambda n: "x".join(map(str, n)))
+def test_scaled_product(gpu, n):
+    """The unpreconditioned iteration's product with the scaling in it: the
+    same values as the copy and the product apart (which captured graphs keep),
+    so the steps are bit-identical, at rows around the wavefront."""
+    import torch
+    n = (n[0], max(n[1], 2), n[2])
+    say("[scaled_product]", n)
+    rng = np.random.default_rng(6)
+    m = rng.standard_normal((int(np.prod(n)), 3))
+    m /= np.linalg.norm(m, axis=1, keepdims=True)
+    res = []
+    for graphs in (0, 1):
+        S = gpu.Solver(gpu.make_grid(2 if n[2] == 1 else 3, n, 1.0 / n[0]),
+                       gpu.default_opts(precision="fp64", krylov="gmres", fine_operator="bsr", graphs=graphs, rtol=1e-10))
+        for _ in range(2):
+            out, s, st = S.step(torch.from_numpy(m).cuda(), 0.1, 1e-3)
+            assert s == gpu.OK
+        res.append((out.cpu().numpy(), st.iters))
+        S.close()
+    assert res[0][1] == res[1][1] and np.array_equal(res[0][0], res[1][0])
