@@ -28,14 +28,19 @@ constexpr int TEAM_W = 32;  // candidates (an XCD has 32 CUs)
 constexpr int TEAM_T = 1024;  // threads of a member
 
 // One per stream that launches teams; zero before the first launch and after
-// every launch (the last candidate to leave clears it).
+// every launch.  When all candidates are members, the last to leave clears it.
+// Otherwise the last one may run on another XCD, and its zeros would wait in
+// that one's L2 while the members' flags are in that of theirs, their order of
+// arrival in memory open: then the last member clears the flags, and the last
+// candidate the rest, past its L2.
 struct TeamState {
   unsigned long long enrol;  // candidates arrived, 7 bits per XCD; bit 63: closed
   unsigned pad0[30];
   unsigned closed;  // (leader's XCD + 1) << 8 | members, once closed
   unsigned pad1[31];
   unsigned left;  // candidates that have left
-  unsigned pad2[31];
+  unsigned pad2[30];
+  unsigned done;  // members that have left a team of fewer; of the team's XCD, as the flags
   unsigned flag[TEAM_W];  // barriers each member has reached
   // totals the members publish for a scan, by slot (written again only after
   // two barriers; not cleared)
@@ -54,6 +59,7 @@ __device__ inline X team_ld(const X* p) {
 struct Team {
   TeamState* s;
   unsigned rank, n, epoch;
+  bool member;
 
   // All threads of the workgroup; false: not a member, and nothing is left to do.
   __device__ bool join(TeamState* st, unsigned pick) {
@@ -90,9 +96,9 @@ struct Team {
     __syncthreads();
     rank = __builtin_amdgcn_readfirstlane(sh[1]);
     n = __builtin_amdgcn_readfirstlane(sh[2]);
-    if (sh[0]) return true;
-    leave();
-    return false;
+    member = sh[0] != 0;
+    if (!member) leave();
+    return member;
   }
 
   // Every thread of every member: a team_ld after it sees the stores before it.
@@ -115,12 +121,27 @@ struct Team {
   __device__ void leave() {
     __syncthreads();
     if (threadIdx.x == 0) {
+      const unsigned all = gridDim.x / 8;
+      const bool whole = member && n == all;
+      if (member && !whole) {
+        // the leader's store of `closed` comes before its count
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (__hip_atomic_fetch_add(&s->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) + 1 == n) {
+          s->done = 0;
+          for (int i = 0; i < TEAM_W; ++i) s->flag[i] = 0;
+        }
+      }
       const unsigned k = __hip_atomic_fetch_add(&s->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (k + 1 == gridDim.x / 8) {  // the last one
+      if (k + 1 < all) return;
+      if (whole) {
         s->enrol = 0;
         s->closed = 0;
         s->left = 0;
         for (int i = 0; i < TEAM_W; ++i) s->flag[i] = 0;
+      } else {
+        __hip_atomic_store(&s->enrol, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&s->closed, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&s->left, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   }
