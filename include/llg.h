@@ -129,6 +129,9 @@ typedef struct {
   int32_t bc;    /* llg_bc; only homogeneous Neumann */
 } llg_grid;
 
+/* The default of llg_opts.tail_nodes. */
+#define LLG_TAIL_NODES_DEFAULT 128
+
 typedef struct {
   double rtol;          /* converged when ||b - A u||_2 <= rtol ||b||_2 (true residual) */
   int32_t restart;      /* FGMRES basis size per cycle, 1..32 */
@@ -161,12 +164,15 @@ typedef struct {
   int32_t stray_field;  /* 1: reserve the stray-field workspace (zero-padded FFT grids and the
                            transformed demagnetizing tensor) for llg_step_field; 2*n-1 padded to a
                            power of two must stay <= 4096 per axis (else UNSUPPORTED) */
-  int32_t tail_nodes;   /* above 0: the small coarse levels (a matrix of at most 2 MB) run their
-                           whole cycle in one launch of a team of workgroups on one XCD; where
-                           that does not apply (deep K-cycles), block-Jacobi levels below the
-                           K-cycle levels (and below level 1 when it is applied through the grid
-                           level), each of at most this many nodes, run their V-cycle in one
-                           workgroup.  Same arithmetic in both.  0: level by level */
+  int32_t tail_nodes;   /* block-Jacobi cycles: the coarse levels below the K-cycle levels (and
+                           below level 1 when it is applied through the grid level), each of at
+                           most this many nodes, run their whole V-cycle in one workgroup with
+                           the level vectors on chip (same arithmetic, one launch instead of
+                           three per level); 0 switches it off.  At the default value (and,
+                           smoothing by Gauss-Seidel, at any above 0) the small coarse levels (a
+                           matrix of at most 2 MB, K-cycle levels too) run in one launch of a
+                           team of workgroups on one XCD instead, unless the K-cycle makes their
+                           list of steps too long */
   int32_t pipeline;     /* 1: FGMRES enqueues the preconditioner and product of the next
                            iteration before the host tests the current one's residual
                            estimate (skipped where convergence is predicted); 0: off */
@@ -196,7 +202,8 @@ typedef struct {
   double kernel_ms;
   int64_t kernel_launches;
   int32_t reorth_passes;  /* Arnoldi steps that needed a second Gram-Schmidt pass */
-  int32_t tail_level;     /* first level of the one-workgroup coarse cycle (opts.tail_nodes); 0 = none */
+  int32_t tail_level;     /* first level of the one-workgroup coarse cycle (opts.tail_nodes); 0 = none
+                             (the levels one by one, or by a team) */
   double kernel_bytes;    /* algorithmic bytes of the timed launches (LLG_KT_LEVEL1: every launch's
                              operands read once and results written once), 0 for the other classes */
 } llg_stats;

@@ -759,11 +759,12 @@ int build_structure(llg_ctx& c, Arena& ar) {
 // block-Jacobi cycles only, below every K-cycle level and below level 1 when
 // it is applied through the grid level, each of at most opts.tail_nodes
 // nodes, at most TAIL_MAX of them, their vectors within the kernel's LDS.
+// None where a team runs the small levels (plan_team).
 template <typename T>
 void plan_tail(llg_ctx& c, TailArgs<T>& a) {
   const llg_opts& o = c.opts;
   c.tail = 0;
-  if (o.tail_nodes <= 0 || o.smoother != LLG_SMOOTHER_JACOBI || c.L < 3 || !c.tail_ok) return;
+  if (c.team > 0 || o.tail_nodes <= 0 || o.smoother != LLG_SMOOTHER_JACOBI || c.L < 3 || !c.tail_ok) return;
   int lo = std::max(1, o.kcycle_depth + 1);
   if (c.f1) lo = std::max(lo, 2);
   const int64_t ts = sizeof(T);
@@ -1295,15 +1296,18 @@ struct TeamList {
 // a level of 0.7 MB (1258 nodes, 3D FP32) 358 in the team and 360 outside,
 // 1.0 MB (2019 nodes, 2D FP64) 162 and 168, 2.2 MB (1881 nodes, 3D FP64) 738
 // and 730, 2.3 MB (8441 nodes, 2D FP32) 350 and 343, 3.4 MB (2D FP64) 177 and
-// 165, 9.1 MB (3D FP32) 384 and 361.  Off with tail_nodes = 0, which asks for
-// the levels one by one.  Called once the structure in c is the set the list
-// is for.
+// 165, 9.1 MB (3D FP32) 384 and 361.  Not with tail_nodes = 0, which asks for
+// the levels one by one, nor (block Jacobi) with a bound other than the default,
+// which asks for one workgroup up to it: a 64^2 step of 15 iterations 2.26 ms
+// that way, 1.72 by the team, 2.16 level by level.  Called once the structure in
+// c is the set the list is for.
 template <typename T>
 void plan_team(llg_ctx& c, void* dev) {
   c.team = 0;
   int s = c.f1 ? 2 : 1;
   while (s < c.L && (c.lv[s].A.n >= 32768 || c.lv[s].nnzb * (int64_t)(9 * sizeof(T) + 4) > TEAM_BYTES)) ++s;
-  if (c.opts.tail_nodes <= 0 || s > c.L - 2) return;
+  const bool one = c.opts.smoother == LLG_SMOOTHER_JACOBI && c.opts.tail_nodes != LLG_TAIL_NODES_DEFAULT;
+  if (c.opts.tail_nodes <= 0 || one || s > c.L - 2) return;
   TeamList<T> t{c, {}};
   t.restrict_to(s, nullptr, t.first_sweep());
   t.correction(s);
@@ -1748,7 +1752,7 @@ void vcycle(llg_ctx& c, int l, const T* b, T* out) {
   }
   const bool coarsest_next = l + 1 == c.L - 1;
   const bool team_next = c.team > 0 && l + 1 == c.team;  // the rest of the cycle by a team
-  const bool tail_next = !team_next && c.tail > 0 && l + 1 == c.tail;  // or in one workgroup
+  const bool tail_next = c.tail > 0 && l + 1 == c.tail;  // or in one workgroup
   const T* rsrc = b;
   {
     KTimer kt(c, LLG_KT_RESIDUAL);
@@ -2339,7 +2343,7 @@ void llg_default_opts(llg_opts* o) {
   o->arnoldi = LLG_ARNOLDI_DCGS2;
   o->krylov = LLG_KRYLOV_FGMRES_AMG;
   o->stray_field = 0;
-  o->tail_nodes = 128;
+  o->tail_nodes = LLG_TAIL_NODES_DEFAULT;
   o->pipeline = 1;
   o->overlap_rebuild = 1;
   o->csr_levels = 1;
@@ -2426,6 +2430,7 @@ llg_status llg_create(const llg_grid* grid, const llg_opts* opts, void* d_worksp
     c->team_xcd = (int)(contexts.fetch_add(1, std::memory_order_relaxed) % 8);
     void* ops1 = c->ops;
     plan_team(*c, ops1);
+    retarget_tail(*c);
     int32_t fl1 = 0;
     if (plan->dbl) {  // the second structure set, built here as well
       c->dbl = true;
