@@ -1834,21 +1834,19 @@ void vcycle_gs(llg_ctx& c, int l, const T* b, T* out) {
     for (int s = 0; s < o.nu_pre; ++s) gs_sweeps<T>(c, L, b, X, true, s == 0);
     LCHK();
   }
+  const T* rsrc = b;
   {
     KTimer kt(c, LLG_KT_RESIDUAL);
-    const T* rsrc = b;
     if (o.nu_pre >= 1) {
       lvl_residual<T>(c, l, 0, b, X, (T*)L.r);
       rsrc = (const T*)L.r;
     }
-    if (team_next)
-      team_correction<T>(c, rsrc);
-    else
-      launch_restrict<T>(st, L.nc, L.mptr, L.mem, rsrc, (T*)Nx.b, nullptr, c.omega, nullptr);
+    // the team restricts rsrc itself
+    if (!team_next) launch_restrict<T>(st, L.nc, L.mptr, L.mem, rsrc, (T*)Nx.b, nullptr, c.omega, nullptr);
     LCHK();
   }
   if (team_next) {
-    // Nx.e holds the coarse correction
+    team_correction<T>(c, rsrc);
   } else if (Nx.kc) {
     kcorrection<T>(c, l + 1);
   } else {
