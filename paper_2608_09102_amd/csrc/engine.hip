@@ -1975,12 +1975,12 @@ void iter_arnoldi(llg_ctx& c, int j) {
 // j - 1 (a finished solve never reads them).
 template <typename T>
 void iteration_head(llg_ctx& c, int j) {
-  if (c.opts.krylov == LLG_KRYLOV_GMRES && c.opts.arnoldi == LLG_ARNOLDI_DCGS2 && !c.fact && !use_graphs(c)) {
-    // both in one launch where z_j is a multiple of slot j
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    kernel_events(c, LLG_KT_OUTER_SPMV, e0, e1);
+  if (c.opts.krylov == LLG_KRYLOV_GMRES && c.opts.arnoldi == LLG_ARNOLDI_DCGS2 && !c.fact && !use_graphs(c) &&
+      c.timed != LLG_KT_OUTER_SPMV) {
+    // both in one launch where z_j is a multiple of slot j (the class of the
+    // product alone, when timed, has it by itself)
     launch_spmv_scaled(c.st, c.lv[0].A, c.Aval, c.V + (int64_t)j * c.ld, c.ks.hinv + j,
-                       (double*)c.Z + (int64_t)j * c.ld, c.w, e0, e1);
+                       (double*)c.Z + (int64_t)j * c.ld, c.w);
     LCHK();
     return;
   }

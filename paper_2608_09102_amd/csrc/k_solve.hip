@@ -2613,14 +2613,10 @@ template void launch_spmv_outer<float>(hipStream_t, Sell, const double*, const f
                                        hipEvent_t);
 
 void launch_spmv_scaled(hipStream_t st, Sell A, const double* val, const double* x, const double* s, double* z,
-                        double* w, hipEvent_t e0, hipEvent_t e1) {
+                        double* w) {
   if (A.n <= 0) return;
   const int tb = tpb_rows(A.n);
-  if (e0)
-    hipExtLaunchKernelGGL(k_spmv_scaled, dim3(nblk(A.n, tb)), dim3(tb), 0, st, e0, e1, 0, A.n, A.sl_ptr, A.col, val,
-                          x, s, z, w);
-  else
-    hipLaunchKernelGGL(k_spmv_scaled, dim3(nblk(A.n, tb)), dim3(tb), 0, st, A.n, A.sl_ptr, A.col, val, x, s, z, w);
+  hipLaunchKernelGGL(k_spmv_scaled, dim3(nblk(A.n, tb)), dim3(tb), 0, st, A.n, A.sl_ptr, A.col, val, x, s, z, w);
 }
 
 void launch_resid_outer(hipStream_t st, Sell A, const double* val, const double* b, const double* u,

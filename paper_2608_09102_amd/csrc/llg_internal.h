@@ -583,7 +583,7 @@ template <typename TZ>
 void launch_spmv_outer(hipStream_t st, Sell A, const double* val, const TZ* z, double* w,
                        hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 void launch_spmv_scaled(hipStream_t st, Sell A, const double* val, const double* x, const double* s, double* z,
-                        double* w, hipEvent_t e0, hipEvent_t e1);  // z = s x, w = A z
+                        double* w);  // z = s x, w = A z
 void launch_resid_outer(hipStream_t st, Sell A, const double* val, const double* b, const double* u,
                         double* r, double* part);
 void launch_norm_part(hipStream_t st, int64_t m, const double* x, double* part);

@@ -25,7 +25,7 @@ def gpu():
     return llg
 
 
-KT_RESIDUAL = 3
+KT_OUTER_SPMV, KT_RESIDUAL = 1, 3
 
 
 @pytest.mark.parametrize("smoother", ("jacobi", "mcgs"))
@@ -49,3 +49,31 @@ def test_residual_class_without_the_team(gpu, smoother):
         say("  tail_nodes %d: %.1f us an iteration in %d intervals" % (t, 1e3 * ms[t], st.kernel_launches))
         S.close()
     assert ms[128] <= ms[0]
+
+
+def test_product_class_is_the_product(gpu):
+    """Unpreconditioned iterations form the scaled basis vector in the
+    product's launch; with the product timed they are two launches."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    say("[product_class_is_the_product]")
+    n = (96, 96, 1)
+    m = np.random.default_rng(2).standard_normal((n[0] * n[1], 3))
+    m = torch.from_numpy(m / np.linalg.norm(m, axis=1, keepdims=True)).cuda()
+    out, runs = [], []
+    for cls in (0, KT_OUTER_SPMV):
+        S = gpu.Solver(gpu.make_grid(2, n, 1.0 / n[0]), gpu.default_opts(krylov="gmres", max_iters=20))
+        S.set_kernel_timing(cls)
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            u, _, st = S.step(m, 0.1, 4e-4, check=False)
+            torch.cuda.synchronize()
+        names = [e.name for e in p.events()]
+        count = [sum(k in x for x in names) for k in ("k_spmv_scaled", "k_spmv_outer")]
+        say("  class %d: %d iterations, %s scaled and plain products" % (cls, st.iters, count))
+        assert st.kernel_launches == (st.iters if cls else 0)
+        out.append(u.cpu().numpy())
+        runs.append(count)
+        S.close()
+    assert runs[0][0] == 20 and runs[0][1] == 0
+    assert runs[1][0] == 0 and runs[1][1] == 20
+    assert np.array_equal(out[0], out[1])
