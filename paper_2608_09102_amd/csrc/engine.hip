@@ -1367,7 +1367,15 @@ void retarget_tail(llg_ctx& c) {
 //
 // Its 100 to 500 launches (2.75 us each on the host) are queued after the
 // setup's, which keep the GPU busy meanwhile: queued before them they left it
-// idle at the start of every step.
+// idle at the start of every step.  From REBUILD_EARLY_NODES on the assembly
+// alone keeps it busy, and the rebuild, as long as a solve of few iterations,
+// starts behind it (after the setup / after the assembly, ms a step: 144^3 MMS
+// 8.7 / 8.6, 160^3 11.1 / 10.6, 176^3 14.0 / 13.7; with many iterations 144^3
+// 23.2 / 23.7, 160^3 30.6 / 30.8, 176^3 40.3 / 40.5).  Above BUILD_ASIDE_NODES the
+// solve is the longer one again and the setup better left alone (192^3 MMS 19.7 /
+// 20.1, 224^3 30.1 / 30.7, 192^3 rough 50.5 / 51.0).
+bool rebuild_early(const llg_ctx& c) { return c.N >= REBUILD_EARLY_NODES && c.N <= BUILD_ASIDE_NODES; }
+
 void take_structure(llg_ctx& c) {
   const int cur = c.set;
   HIPX(hipStreamWaitEvent(c.st, c.built[cur], 0));
@@ -1393,7 +1401,7 @@ void rebuild_next(llg_ctx& c) {
   ar.st = c.aux;
   ar.flag_word = 1;
   ar.keep_grid = true;
-  ar.team_from = c.build_from;
+  if (c.N <= BUILD_ASIDE_NODES) ar.team_from = c.build_from;
   try {
     (void)build_structure(c, ar);
   } catch (...) {
@@ -1447,6 +1455,7 @@ void setup_values(llg_ctx& c, const double* m, const double* mprev, const double
     }
     LCHK();
   }
+  if (beside && rebuild_early(c)) rebuild_next(c);
   if (field) {  // explicit field terms of the right-hand side (field 2: with the stray field)
     double* h = field == 2 ? stray_room(c.fd, c.fwork) : nullptr;
     if (h) launch_stray(st, c.fd, m, mprev, c.nhat, c.fwork, h);
@@ -1482,7 +1491,7 @@ void setup_values(llg_ctx& c, const double* m, const double* mprev, const double
   launch_dense_scatter<T>(st, C.A, (const T*)C.val, c.dense);
   launch_gauss_jordan(st, c.nd, c.dense, c.piv, c.flags);
   LCHK();
-  if (beside) rebuild_next(c);
+  if (beside && !rebuild_early(c)) rebuild_next(c);
 }
 
 // Graphs are used unless switched off, or a kernel class other than the outer

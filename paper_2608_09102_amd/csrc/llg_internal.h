@@ -203,6 +203,16 @@ constexpr int BUILD_LDS_ROW = 1024;  // LDS of a row's table, 16 threads a row
 // 8.39 / 8.28 / 8.64 ms, 1024^2 23.5 / 23.3 / 23.8, 131 x 75 x 97 6.79 / 6.74 /
 // 7.23, 41^3 3.04 / 3.09 / 3.46 ms.
 constexpr int64_t BUILD_NODES = 24576;
+// The largest grid whose small levels a team builds beside the solve: the XCD
+// that it holds slows every kernel of the solve (with the per-pass kernels / with
+// the team, ms a step: 192^3 MMS 19.7 / 20.3, 224^3 30.1 / 30.7, 256^3 45.4 / 45.8
+// in FP32-AMG and 63.8 / 64.3 in FP64, 192^3 rough 50.5 / 51.3).  Smaller grids
+// with few iterations wait for the launches that it saves (176^3 MMS 14.6 / 14.0,
+// 128^3 7.4 / 6.8; with many iterations 176^3 39.8 / 40.3, 128^3 17.1 / 17.4).
+constexpr int64_t BUILD_ASIDE_NODES = 6 << 20;
+// Grids from here on queue the rebuild after the assembly, smaller ones and those
+// above BUILD_ASIDE_NODES after the whole setup (see rebuild_next).
+constexpr int64_t REBUILD_EARLY_NODES = 3 << 20;
 struct TeamState;
 void launch_team_build(hipStream_t st, TeamState* ts, int pick, const BuildLevel* lv, int nlev, int npass,
                        int32_t bnum, int32_t bden, int32_t* flag, int32_t bit, bool aside);

@@ -26,6 +26,7 @@ namespace llg {
 
 constexpr int TEAM_W = 32;  // candidates (an XCD has 32 CUs)
 constexpr int TEAM_T = 1024;  // threads of a member
+constexpr int TEAM_POLLS = 64;
 
 // One per stream that launches teams; zero before the first launch and after
 // every launch.  When all candidates are members, the last to leave clears it.
@@ -62,7 +63,8 @@ struct Team {
   bool member;
 
   // All threads of the workgroup; false: not a member, and nothing is left to do.
-  __device__ bool join(TeamState* st, unsigned pick) {
+  // polls: how long the first waits for the others, about 0.3 us each.
+  __device__ bool join(TeamState* st, unsigned pick, int polls = TEAM_POLLS) {
     __shared__ unsigned sh[3];
     s = st;
     epoch = 0;
@@ -73,8 +75,8 @@ struct Team {
           __hip_atomic_fetch_add(&s->enrol, 1ull << (7 * x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       unsigned ok = 0, r = (unsigned)(old >> (7 * x)) & 127u, cnt = 0;
       if (!(old >> 63)) {
-        if (old == 0) {  // the first: closes when all are here, or after about 20 us
-          for (int k = 0; k < 64; ++k)
+        if (old == 0) {  // the first: closes when all are here, or after that time
+          for (int k = 0; k < polls; ++k)
             if (((team_ld(&s->enrol) >> (7 * x)) & 127u) >= gridDim.x / 8) break;
           const unsigned long long v =
               __hip_atomic_fetch_or(&s->enrol, 1ull << 63, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

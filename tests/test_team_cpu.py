@@ -126,7 +126,8 @@ MAIN = r"""
 using namespace llg;
 static TeamState state;
 static int steps, arrived[64], ranks, members, teams, gone, bad;
-struct Job { int group, lane, xcd, late, lag; };
+static int polls;
+struct Job { int group, lane, xcd, late, lag; };  // late 1: after the others have left, 2: after 30 ms
 
 static void* run(void* a) {
   const Job j = *(Job*)a;
@@ -135,10 +136,11 @@ static void* run(void* a) {
   threadIdx.x = j.lane;
   blockIdx.x = 8 * j.group + 3;
   gridDim.x = 8 * sim::GROUPS;
-  if (j.late)  // starts when the others have left
+  if (j.late == 2) usleep(30000);
+  if (j.late == 1)
     while (__atomic_load_n(&gone, __ATOMIC_SEQ_CST) < sim::GROUPS - 1) usleep(200);
   Team t;
-  if (t.join(&state, 3)) {
+  if (t.join(&state, 3, polls)) {
     if (j.lane == 0) {
       __atomic_fetch_add(&members, 1, __ATOMIC_SEQ_CST);
       if (__atomic_fetch_or(&ranks, 1 << t.rank, __ATOMIC_SEQ_CST) >> t.rank & 1) bad |= 1;
@@ -158,12 +160,13 @@ static void* run(void* a) {
   return nullptr;
 }
 
-int main(int argc, char** argv) {  // order of write-back; per launch: barriers, then xcd, late, lag of each workgroup
+int main(int argc, char** argv) {  // order of write-back; per launch: barriers, polls, then xcd, late, lag of each workgroup
   for (int g = 0; g < sim::GROUPS; ++g) pthread_barrier_init(&sim::bar[g], nullptr, sim::LANES);
   const bool up = atoi(argv[1]) != 0;
   int a = 2;
   for (int launch = 0; a < argc; ++launch) {
     steps = atoi(argv[a++]);
+    polls = atoi(argv[a++]);
     memset(arrived, 0, sizeof(arrived));
     ranks = members = teams = gone = bad = 0;
     std::vector<Job> jobs;
@@ -202,14 +205,16 @@ def model(tmp_path_factory):
     return str(exe)
 
 
-# per launch (barriers, then the XCD, "starts when the others have left" and
-# "is slow to each barrier" of four workgroups)
+# per launch: barriers, and of four workgroups the XCD and L "starts when the
+# others have left", S "starts late", 1 "is slow to each barrier"; the polls of
+# the first and, where these suffice for all to join, the members
 LAUNCHES = {
     "one XCD": [(3, "00 00 00 00"), (4, "00 01 00 00"), (2, "00 00 00 01")],
     "a late one on another XCD leaves last": [(3, "00 00 00 1L"), (3, "00 01 00 0L"), (3, "01 00 00 00")],
     "a late one on the team's XCD leaves last": [(3, "00 00 00 0L"), (3, "00 01 00 0L")],
     "teams on changing XCDs": [(2, "00 00 00 1L"), (3, "10 11 10 0L"), (4, "00 01 00 01"), (1, "10 11 11 10")],
     "no barrier": [(0, "00 00 00 1L"), (2, "00 01 00 00")],
+    "a slow start": [(3, "00 0S 00 00", 4000, 4), (3, "00 0S 00 01"), (3, "00 01 00 0S", 4000, 4)],
     "a mixed start": [(3, "00 10 00 10"), (3, "00 01 00 11"), (3, "20 01 21 00"), (3, "00 01 00 01")],
 }
 
@@ -218,9 +223,13 @@ LAUNCHES = {
 @pytest.mark.parametrize("name", LAUNCHES)
 def test_team_protocol(model, name, up):
     args = [str(up)]
-    for steps, groups in LAUNCHES[name]:
-        args.append(str(steps))
+    for steps, groups, *polls in LAUNCHES[name]:
+        args += [str(steps), str(polls[0] if polls else 64)]
         for g in groups.split():
-            args += [g[0], "1" if g[1] == "L" else "0", "1" if g[1] == "1" else "0"]
+            args += [g[0], {"L": "1", "S": "2"}.get(g[1], "0"), "1" if g[1] == "1" else "0"]
     r = subprocess.run([model] + args, capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
+    members = [int(x.split()[2]) for x in r.stdout.splitlines()]
+    assert len(members) == len(LAUNCHES[name])
+    for got, (_, _, *polls) in zip(members, LAUNCHES[name]):
+        assert not polls or got == polls[1]
