@@ -60,7 +60,6 @@ __device__ inline X team_ld(const X* p) {
 struct Team {
   TeamState* s;
   unsigned rank, n, epoch;
-  bool member;
 
   // All threads of the workgroup; false: not a member, and nothing is left to do.
   // polls: how long the first waits for the others, about 0.3 us each.
@@ -98,9 +97,9 @@ struct Team {
     __syncthreads();
     rank = __builtin_amdgcn_readfirstlane(sh[1]);
     n = __builtin_amdgcn_readfirstlane(sh[2]);
-    member = sh[0] != 0;
-    if (!member) leave();
-    return member;
+    if (sh[0]) return true;
+    depart<false>();
+    return false;
   }
 
   // Every thread of every member: a team_ld after it sees the stores before it.
@@ -119,13 +118,16 @@ struct Team {
     __syncthreads();
   }
 
-  // Every candidate, once, when it needs the state no more.
-  __device__ void leave() {
+  // Every member, once, when it needs the state no more.
+  __device__ void leave() { depart<true>(); }
+
+  template <bool MEMBER>
+  __device__ void depart() {
     __syncthreads();
     if (threadIdx.x == 0) {
       const unsigned all = gridDim.x / 8;
-      const bool whole = member && n == all;
-      if (member && !whole) {
+      const bool whole = MEMBER && n == all;
+      if (MEMBER && !whole) {
         // the leader's store of `closed` comes before its count
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (__hip_atomic_fetch_add(&s->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) + 1 == n) {
