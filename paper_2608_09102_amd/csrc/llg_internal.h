@@ -164,7 +164,6 @@ void launch_slice_width(hipStream_t st, int64_t n, const int32_t* rows, const in
 void launch_sell_cols(hipStream_t st, int64_t n, const int32_t* rows, const int32_t* brp, const int32_t* bci,
                       const int32_t* sl_ptr, int32_t* col);
 
-// prop[i] = proposed partner or -1; *any is set non-zero when some node proposes
 // Matching state of a node, one 8-byte record so that a candidate costs one
 // load: its largest edge weight and its mate (-1 while unmatched; the
 // proposal rounds mark a free node without candidates -2 in the mate array
@@ -240,6 +239,7 @@ void launch_node_rank(hipStream_t st, int64_t n, uint64_t salt, uint64_t* rank);
 // ns[i] = {max_k w_ik, -1}; mate[i] = -1; prop[i] = -1 (no proposal yet)
 void launch_match_init(hipStream_t st, int64_t n, const int32_t* grp, const int32_t* gw, uint64_t salt,
                        NodeSt* ns, int32_t* mate, int32_t* prop);
+// prop[i] = proposed partner or -1; *any is set non-zero when some node proposes
 void launch_propose(hipStream_t st, int64_t n, const int32_t* grp, const int32_t* gci, const int32_t* gw,
                     int32_t* mate, const NodeSt* ns, uint64_t salt, int32_t bnum, int32_t bden, int32_t* prop,
                     int32_t* any, int lanes);
@@ -319,13 +319,11 @@ void launch_fact_blocks(hipStream_t st, int nx, int ny, int nz, double inv_h2, c
                         double* Mh, T* K);
 
 // Where a Galerkin product reads the fine blocks, and where it leaves a copy
-// of the coarse ones.  fk != NULL: the fine level is the factored grid level,
-// whose block (i, j) is the identity when j == i and K_i otherwise; K_i is
-// read from knm (node-major, nine contiguous values) when it is not NULL,
-// else from fk.  Otherwise the blocks are read from fvt (the level's blocks
-// in slot order, nine contiguous values per slot) when it is not NULL, else
-// from the sliced-ELL values fval.  cvt != NULL receives the coarse blocks
-// in slot order.
+// of the coarse ones.  fvt != NULL: a coarse level, its blocks in CSR order.
+// knm != NULL: the factored grid level, whose block (i, j) is the identity when
+// j == i and K_i otherwise.  Else the grid level's sliced-ELL values fval, of
+// which a row's off-diagonal blocks are all the same.  cvt != NULL receives the
+// coarse blocks in CSR order.
 template <typename T>
 struct GalSrc {
   const T* fval = nullptr;     // fine blocks, sliced ELL (the grid level stored as BSR)
@@ -342,7 +340,7 @@ template <typename T>
 void launch_galerkin(hipStream_t st, Sell C, T* cval, T* cdinv, const int32_t* mptr, const int32_t* mem, Sell F,
                      const int32_t* agg, const GalSrc<T>& g);
 
-// one-time kernel attribute setup (large dynamic LDS for the coarsest inverse)
+// one-time kernel attribute setup (the dynamic LDS of the build team)
 void init_kernel_attributes();
 
 // coarsest level: dense copy and in-place Gauss-Jordan inverse
