@@ -1707,8 +1707,9 @@ __device__ inline bool team_level(Team& t, const BuildLevel& L, int32_t* sh) {
 
 // Beside another stream's work (NT = 512) the first member waits for the others
 // up to 0.3 ms: among kernels that fill the chip the places come one by one, and
-// after 20 us half of the builds at 224^3 and 256^3 ran with 1 to 5 members, for
-// longer than the step beside them (224^3: 34.4 ms a step, 30.8 with all 32).
+// after 20 us 26 of 33 builds at 224^3 and 14 of 27 at 256^3 ran with 1 to 5
+// members, for longer than the step beside them (224^3: 34.4 ms a step, 30.8 with
+// all 32).
 template <int NT>
 __global__ void __launch_bounds__(NT) k_team_build(TeamState* ts, int pick, const BuildLevel* __restrict__ lv,
                                                    int nlev, int npass, int32_t bnum, int32_t bden, int32_t* flag,
