@@ -76,7 +76,7 @@ struct Team {
       if (!(old >> 63)) {
         if (old == 0) {  // the first: closes when all are here, or after that time
           for (int k = 0; k < polls; ++k)
-            if (((team_ld(&s->enrol) >> (7 * x)) & 127u) >= gridDim.x / 8) break;
+            if (((team_ld(&s->enrol) >> (7 * x)) & 127u) >= TEAM_W) break;
           const unsigned long long v =
               __hip_atomic_fetch_or(&s->enrol, 1ull << 63, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           cnt = (unsigned)(v >> (7 * x)) & 127u;
@@ -125,8 +125,7 @@ struct Team {
   __device__ void depart() {
     __syncthreads();
     if (threadIdx.x == 0) {
-      const unsigned all = gridDim.x / 8;
-      const bool whole = MEMBER && n == all;
+      const bool whole = MEMBER && n == TEAM_W;
       if (MEMBER && !whole) {
         // the leader's store of `closed` comes before its count
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -136,7 +135,7 @@ struct Team {
         }
       }
       const unsigned k = __hip_atomic_fetch_add(&s->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (k + 1 < all) return;
+      if (k + 1 < TEAM_W) return;
       if (whole) {
         s->enrol = 0;
         s->closed = 0;

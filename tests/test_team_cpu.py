@@ -107,7 +107,7 @@ inline bool all(bool b, unsigned lane) {
   return r;
 }
 }  // namespace sim
-inline thread_local sim::Dim threadIdx, blockIdx, gridDim;
+inline thread_local sim::Dim threadIdx, blockIdx;
 #define __builtin_amdgcn_s_getreg(r) ((unsigned)sim::xcd)
 #define __builtin_amdgcn_readfirstlane(v) sim::first((v), threadIdx.x)
 #define __syncthreads() sim::sync()
@@ -135,7 +135,6 @@ static void* run(void* a) {
   sim::xcd = j.xcd;
   threadIdx.x = j.lane;
   blockIdx.x = 8 * j.group + 3;
-  gridDim.x = 8 * sim::GROUPS;
   if (j.late == 2) usleep(30000);
   if (j.late == 1)
     while (__atomic_load_n(&gone, __ATOMIC_SEQ_CST) < sim::GROUPS - 1) usleep(200);
@@ -191,7 +190,8 @@ def model(tmp_path_factory):
     d = tmp_path_factory.mktemp("team")
     (d / "hip").mkdir()
     (d / "hip" / "hip_runtime.h").write_text(MODEL)
-    src = open(TEAM_H).read()
+    src, n = re.subn(r"TEAM_W = 32;", "TEAM_W = 4;", open(TEAM_H).read())
+    assert n == 1
     src = re.sub(r'asm volatile\("s_waitcnt vmcnt\(0\)"[^;]*;', ";", src)  # the model's stores are done at once
     # a plain store stays in the XCD's L2 as one of workgroup scope does
     src = re.sub(r"\bs->(\w+(?:\[\w+\])?) = ([^;]+);", r"sim::store(&s->\1, \2, 1);", src)
